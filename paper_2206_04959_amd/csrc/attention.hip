@@ -8,7 +8,7 @@
 // seq x seq score matrix never reaches HBM (the method published as
 // FlashAttention, Dao et al. 2022; the gfx950 tiling below is our own).
 //   * forward: a workgroup owns 64 query rows of one (batch, head); its four
-//     waves are two groups of 32 rows times the even and odd 64-key blocks,
+//     waves are two groups of 32 rows times the even and odd 32-key tiles,
 //     merged at the end with the online-softmax merge.  A wave computes the
 //     transposed score tile S^T = K Q^T so that each lane owns one query
 //     column; the softmax then needs only a lane-half exchange, and P^T stays
@@ -27,7 +27,7 @@
 //
 // fp32 check mode: one thread per query (or key) row, fp32 throughout.
 #include <math.h>
-
+#include <algorithm>
 #include <atomic>
 #include <type_traits>
 
@@ -125,6 +125,40 @@ __device__ __forceinline__ bf16x8_t frag_kc(const bf16_t* p) { return *reinterpr
 // kernels need nothing else to work on such a group.
 __device__ __forceinline__ int seq_index(int z, int Bm, int mstride) { return (z / Bm) * mstride + z % Bm; }
 
+// Work of one workgroup: sequence, head and 64-row block.
+struct AttnSlot {
+  int z, hh, blk;  // launch batch, head, row block counted from the one with the most work
+};
+
+// Order of the grid's workgroups (1-D grid of H * B * n_blk).  Workgroups go to
+// the 8 XCDs round-robin; each XCD takes whole (sequence, head) pairs, so that a
+// pair's streamed rows are fetched into one L2 only, in chunks of `chunk` pairs
+// whose rows fit that L2 together, and within a chunk the blocks with the most
+// work first.  The pairs left over by the division come before that, their
+// blocks spread over all XCDs.  `fold`: the second half of the blocks runs in
+// reverse order (see attn_order).
+struct AttnOrder {
+  int n_blk, chunk, fold;
+};
+__device__ __forceinline__ AttnSlot attn_slot(int id, int H, int n_pairs, const AttnOrder& ord) {
+  const int full = n_pairs >> 3, left = n_pairs & 7;
+  int pair, blk;
+  if (id < left * ord.n_blk) {
+    pair = full * 8 + id % left;
+    blk = id / left;
+  } else {
+    id -= left * ord.n_blk;
+    const int x = id & 7, i = id >> 3;  // i-th workgroup of one XCD
+    const int c = i / (ord.chunk * ord.n_blk), in = i - c * ord.chunk * ord.n_blk;
+    const int c0 = c * ord.chunk, cs = min(ord.chunk, full - c0);
+    pair = x * full + c0 + in % cs;
+    blk = in / cs;
+  }
+  const int half = (ord.n_blk + 1) >> 1;
+  if (ord.fold && blk >= half) blk = ord.n_blk - 1 - (blk - half);
+  return {pair / H, pair % H, blk};
+}
+
 // LDS stages of the bf16 kernels (each four tiles: two 64-row blocks of two
 // tensors).  One stage keeps a workgroup small enough (53 KB at d = 96) to share
 // a CU with a GEMM workgroup of the other stream; the loads of the next block
@@ -139,171 +173,320 @@ template <int D>
 constexpr size_t attn_lds_bytes() { return (size_t)kAttnStages * 4 * AttnTile<D>::BYTES; }
 
 // ---------------------------------------------------------------------------
-// bf16 forward.  A workgroup owns 64 query rows of one (batch, head); wave w
-// takes the 32 rows of group w % 2 against the even (w < 2) or odd 64-key
-// blocks, and the two halves are merged at the end (online-softmax merge).
-// Each stage holds the K and V tiles of two key blocks.
+// 32-row tiles for the streaming operands.  A [32 rows][D] bf16 tile is stored
+// without padding; the 16-byte chunk c of row r sits in slot pos(c, r) of its
+// row, chosen so that both kinds of fragment reads are free of bank conflicts
+// (64 banks of 4 bytes): a row read takes one chunk of 16 consecutive rows per
+// pass, a transposing read four neighbouring chunks of four consecutive rows.
+// pos() depends on r mod 16 only.
 // ---------------------------------------------------------------------------
 template <int D>
-__global__ void __launch_bounds__(256) attn_fwd_bf16(int S, int H, int Bm, int mstride, const bf16_t* __restrict__ qkv,
-                                                     bf16_t* __restrict__ o, float* __restrict__ lse,
-                                                     float scale_log2) {
-  using TT = AttnTile<D>;
-  constexpr int LD = TT::LD, KS = D / 16, DT = D / 32, TB = TT::BYTES;
-  extern __shared__ __align__(16) char smem[];  // [stage][K blk a, K blk b, V blk a, V blk b]
+struct SwTile {
+  static constexpr int ROWB = D * 2;        // bytes per row
+  static constexpr int CH = D / 8;          // 16-byte chunks per row
+  static constexpr int BYTES = 32 * ROWB;
+  static constexpr int NI = BYTES / 1024;   // 16-byte-per-lane wave loads per tile
+  static constexpr __host__ __device__ int pos(int c, int r) {
+    if constexpr (D == 64) return c ^ ((((r >> 1) & 1) << 2) | ((r >> 2) & 3));
+    else if constexpr (D == 128) return c ^ (((r & 3) << 2) | ((r >> 2) & 3));
+    else return (c + ((r >> 2) & 3)) % CH;
+  }
+  static constexpr __host__ __device__ int chunk_at(int p, int r) {  // inverse of pos in c
+    if constexpr (D == 96) return (p + CH - ((r >> 2) & 3)) % CH;
+    else return pos(p, r);
+  }
+};
 
-  // Grid (heads, sequences, row blocks), row block slowest: the whole grid
-  // runs longest rows first.
-  const int b = seq_index(blockIdx.y, Bm, mstride), hh = blockIdx.x;
-  const int qt = gridDim.z - 1 - blockIdx.z;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
+// 16-byte-per-lane global -> LDS load: lane i writes LDS bytes [lds_addr + 16 i,
+// lds_addr + 16 i + 16).  Inline assembly, because the compiler would make
+// every later LDS read wait for it; the kernels order these loads themselves
+// (dma_wait).  An M0 write needs one wait state before it.
+typedef int32_t i32x4_t __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ i32x4_t buffer_words(const void* p) {
+  const uint64_t a = reinterpret_cast<uint64_t>(p);
+  return i32x4_t{(int32_t)__builtin_amdgcn_readfirstlane((uint32_t)a),
+                 (int32_t)__builtin_amdgcn_readfirstlane((uint32_t)((a >> 32) & 0xffffu)), 0x7fffffff, 0x00020000};
+}
+__device__ __forceinline__ void dma16(i32x4_t rsrc, uint32_t lds_addr, uint32_t voff) {
+  asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
+               :
+               : "v"(voff), "s"(rsrc), "{m0}"(lds_addr)
+               : "memory");
+}
+// Wait until at most N of this wave's vector-memory operations are outstanding.
+template <int N>
+__device__ __forceinline__ void dma_wait() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+// Wait for this wave's LDS reads (before a load overwrites what they read).
+__device__ __forceinline__ void lds_wait() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// One wave's plan for loading a tile from rows of stride `gs` elements.
+template <int D>
+struct TileDma {
+  uint32_t voff[SwTile<D>::NI];
+  __device__ __forceinline__ void init(size_t gs, int lane) {
+#pragma unroll
+    for (int q = 0; q < SwTile<D>::NI; ++q) {
+      const int idx = q * 64 + lane, r = idx / SwTile<D>::CH, p = idx % SwTile<D>::CH;
+      voff[q] = (uint32_t)((size_t)r * gs * 2) + (uint32_t)SwTile<D>::chunk_at(p, r) * 16u;
+    }
+  }
+  __device__ __forceinline__ void issue(uint32_t lds_addr, const bf16_t* rows) const {
+    const i32x4_t rsrc = buffer_words(rows);
+#pragma unroll
+    for (int q = 0; q < SwTile<D>::NI; ++q) dma16(rsrc, lds_addr + q * 1024, voff[q]);
+  }
+};
+
+// Fragment reads of a tile: row(ks) is the MFMA operand with lane l holding row
+// l % 32 and columns 16 ks + 8 (l / 32) + 0..7; tr(kb, dt) the transposed one,
+// lane l holding column 32 dt + l % 32 and rows kb + 4 (l / 32) + 0..3, then
+// kb + 8 + 4 (l / 32) + 0..3 (the row order of an accumulator reused as the
+// 16-deep operand), from two transposing LDS reads.
+template <int D>
+struct TileFrag {
+  using ST = SwTile<D>;
+  int ro[D / 16], lo[D / 32], hi[D / 32];
+  __device__ __forceinline__ void init(int lane) {
+    const int l32 = lane & 31, hf = lane >> 5;
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks) ro[ks] = l32 * ST::ROWB + ST::pos(2 * ks + hf, l32) * 16;
+    const int r = hf * 4 + ((lane & 15) >> 2), cl = ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1);
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt) {
+      lo[dt] = r * ST::ROWB + ST::pos(dt * 4 + cl, r) * 16 + (lane & 1) * 8;
+      hi[dt] = (r + 8) * ST::ROWB + ST::pos(dt * 4 + cl, r + 8) * 16 + (lane & 1) * 8;
+    }
+  }
+  __device__ __forceinline__ bf16x8_t row(const char* tile, int ks) const {
+    return *reinterpret_cast<const bf16x8_t*>(tile + ro[ks]);
+  }
+  __device__ __forceinline__ bf16x8_t tr(const char* tile, int kb, int dt) const {
+    const char* t = tile + kb * ST::ROWB;
+    const s16x4_t a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((MERAK_LDS s16x4_t*)(t + lo[dt]));
+    const s16x4_t b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((MERAK_LDS s16x4_t*)(t + hi[dt]));
+    const s16x8_t v = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+    return __builtin_bit_cast(bf16x8_t, v);
+  }
+};
+
+// Keeps a value's computation where it is written (between two MFMAs), rather
+// than sunk to its use.
+__device__ __forceinline__ float pinned(float v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
+// Value of the other half-wave's matching lane combined with this lane's.
+__device__ __forceinline__ float half_max(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float half_sum(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// Waits for this wave's loads and joins the workgroup barrier: the tiles that
+// were on their way can be read, and all waves are done with the tiles of the
+// step before.
+__device__ __forceinline__ void step_barrier() {
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// ---------------------------------------------------------------------------
+// bf16 forward.  A workgroup owns 64 query rows of one (batch, head); wave w
+// takes the 32 rows of group w % 2 against the even (w < 2) or odd 32-key
+// tiles, and the two halves are merged at the end (online-softmax merge).
+//
+// The matrix and the vector units take about equal time here, so each wave
+// overlaps them itself: step t issues the MFMAs of S(t + 1) and of the
+// P V product of tile t one at a time between the softmax instructions of tile
+// t.  K and V tiles sit in two-slot rings, loaded one step ahead; one barrier
+// per step.  Small tiles and 157 registers (d = 96) let three workgroups share
+// a CU.  What bounds it: on small grids the longest row block's chain (about
+// 1400 cycles a step), on large ones the vector unit (16 exponentials, 60 other
+// instructions and 12 MFMAs of 32 cycles per 32 x 32 tile).  Against 64-key
+// blocks with padded tiles and no overlap inside a wave: 4 x 1024 x 8 heads of
+// 96 18.8 -> 16.0 us, 2 x 2048 x 6 of 128 39.0 -> 29.6 us, 4 x 2048 x 25 of 96
+// 167 -> 129 us.  A third slot was 4% faster on the first of these and 6%
+// slower on the last (two workgroups per CU).
+// ---------------------------------------------------------------------------
+template <int D>
+constexpr size_t fwd_lds_bytes() { return (size_t)8 * SwTile<D>::BYTES; }
+
+template <int D>
+__global__ void __launch_bounds__(256, 2) attn_fwd_bf16(int S, int H, int Bm, int mstride,
+                                                        const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o,
+                                                        float* __restrict__ lse, float scale_log2, int n_pairs,
+                                                        AttnOrder ord) {
+  using ST = SwTile<D>;
+  constexpr int KS = D / 16, DT = D / 32, TB = ST::BYTES;
+  extern __shared__ __align__(16) char smem[];  // [slot][K even, K odd, V even, V odd]
+
+  const AttnSlot slot = attn_slot(blockIdx.x, H, n_pairs, ord);
+  const int b = seq_index(slot.z, Bm, mstride), hh = slot.hh;
+  const int qt = ord.n_blk - 1 - slot.blk;  // the last rows see the most keys
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qg = wave & 1, kh = wave >> 1;
   const int q0 = qt * 64 + qg * 32;
   const int q = q0 + l32;
   const size_t rs = (size_t)3 * H * D;
   const bf16_t* base = qkv + (size_t)b * S * rs;
   const bf16_t* Qp = base + hh * D;
-  const bf16_t* Kp = base + (size_t)H * D + hh * D;
-  const bf16_t* Vp = base + (size_t)2 * H * D + hh * D;
 
+  // Wave w loads tile w of a step: K (w < 2) or V of the even or odd keys.
+  const int nt = qt + 1;  // steps; tile t of half kh holds keys 64 t + 32 kh ..
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(MERAK_LDS char*)smem) + wave * TB;
+  const bf16_t* lsrc = base + (size_t)(1 + kh) * H * D + hh * D + (size_t)(wave & 1) * 32 * rs;
+  TileDma<D> dma;
+  dma.init(rs, lane);
+  auto load = [&](int t) {
+    if (t < nt) dma.issue(lds0 + (t & 1) * 4 * TB, lsrc + (size_t)t * 64 * rs);
+  };
+  TileFrag<D> fr;
+  fr.init(lane);
   bf16x8_t qf[KS];
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) qf[ks] = frag_kc(Qp + (size_t)q * rs + ks * 16 + hf * 8);
+  load(0);
+  // The wait for the query fragments belongs here: left to their first use it
+  // would also cover the tile loads.
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qf[ks]));
 
-  const int n_kb = qt + 1;  // key blocks 0..qt reach the tile's last row
-  const int n_it = (n_kb + 1) / 2;
-  TileLoad<D> tl;
-  tl.init(rs, lane);
-  const bf16_t* lsrc = (wave >> 1) ? Vp : Kp;
-  auto load_stage = [&](int it, int stage) {  // wave w: tile w of the stage
-    const int blk = 2 * it + (wave & 1);
-    if (blk < n_kb) tl.issue(smem + (stage * 4 + wave) * TB, lsrc + (size_t)blk * 64 * rs);
-  };
-
-  f32x16_t oacc[DT];
+  f32x16_t oacc[DT], s;
 #pragma unroll
   for (int t = 0; t < DT; ++t)
 #pragma unroll
     for (int r = 0; r < 16; ++r) oacc[t][r] = 0.0f;
-  float m = -INFINITY, l = 0.0f;
+  float m = -INFINITY, nm = 0.0f;  // running maximum (scaled, log2 units); -m, 0 before the first score
+  float l[2] = {0.0f, 0.0f};       // sum, in two parts
 
-  // S = K Q^T of key block kb (LDS tile Kt) for this wave's 32 queries.
-  auto scores = [&](const char* Kt, f32x16_t (&s)[2]) {
+  // Causal mask of tile t's scores: x[r] is key 64 t + 32 kh + (r/4)*8 + 4*hf +
+  // r%4, query q.  Only the last tiles reach past a query.
+  auto mask = [&](f32x16_t& x, int t) {
+    const int lim = q - (64 * t + 32 * kh) - hf * 4;
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
+    for (int r = 0; r < 16; ++r)
+      if ((r >> 2) * 8 + (r & 3) > lim) x[r] = -INFINITY;
+  };
+  // The running maximum after a tile whose own maximum (this lane's half) is mx.
+  auto new_max = [&](float mx) {
+    mx = half_max(mx) * scale_log2;
+    if (__ballot(mx > m)) {  // rescale only when some row's maximum grew
+      const float mnew = fmaxf(m, mx);
+      // a row without any score yet keeps its (zero) sums: no -inf - -inf
+      nm = mnew == -INFINITY ? 0.0f : -mnew;
+      const float alpha = __builtin_amdgcn_exp2f(m + nm);
+      m = mnew;
+      l[0] *= alpha;
+      l[1] *= alpha;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s[t][r] = 0.0f;
+      for (int u = 0; u < DT; ++u)
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-        s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_row<LD>(Kt, t * 32 + l32, ks * 16 + hf * 8), qf[ks],
-                                                       s[t], 0, 0, 0);
+        for (int r = 0; r < 16; ++r) oacc[u][r] *= alpha;
     }
   };
-  // Causal mask, online softmax and O^T += V^T P^T with key block kb (tile Vt).
-  auto softmax_pv = [&](const char* Vt, int k0, f32x16_t (&s)[2]) {
-    // s[t][r]: key k0 + t*32 + (r/4)*8 + 4*hf + r%4, query q.  Only a block
-    // that reaches past the wave's first query needs the causal mask.
-    float mloc = -INFINITY;
-    if (k0 + 63 > q0) {
+
+  step_barrier();
+  if (wave < 2) load(1);
+  {
+    const char* Kt = smem + kh * TB;
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
+    for (int r = 0; r < 16; ++r) s[r] = 0.0f;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = k0 + t * 32 + (r >> 2) * 8 + hf * 4 + (r & 3);
-          const float v = key > q ? -INFINITY : s[t][r] * scale_log2;
-          s[t][r] = v;
-          mloc = fmaxf(mloc, v);
-        }
-    } else {
+    for (int ks = 0; ks < KS; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr.row(Kt, ks), qf[ks], s, 0, 0, 0);
+    if (nt == 1) mask(s, 0);
+    float mx = s[0];
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
+    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
+    new_max(mx);
+  }
+
+  // Step t, with t % 2 = SLOT known at compile time (tile addresses become
+  // instruction offsets).
+  auto step = [&](int t, auto slot_c) {
+    constexpr int SLOT = decltype(slot_c)::value;
+    // K(t + 1) and V(t) are there; K(t) and V(t - 1) are no longer needed
+    step_barrier();
+    load(wave < 2 ? t + 2 : t + 1);
+    const char* Kt = smem + ((SLOT ^ 1) * 4 + kh) * TB;  // past the last step: stale, its scores are not used
+    const char* Vt = smem + (SLOT * 4 + 2 + kh) * TB;
+    bf16x8_t kf[KS], vf[2][DT], pb[2];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          s[t][r] *= scale_log2;
-          mloc = fmaxf(mloc, s[t][r]);
-        }
+    for (int ks = 0; ks < KS; ++ks) kf[ks] = fr.row(Kt, ks);
+    // Softmax of tile t in stages, so that no instruction waits for the one
+    // before it: all exponents first (while the K fragments are on their way),
+    // the exponentials between the MFMAs, each added to the sum two later.
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      s[r] = pinned(fmaf(s[r], scale_log2, nm));
     }
-    mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64));
-    const float mnew = fmaxf(m, mloc);
-    if (__ballot(mnew > m)) {  // rescale only when some row's maximum grew
-      const float alpha = __builtin_amdgcn_exp2f(m - mnew);
-      l *= alpha;
+    auto prob = [&](int r) {
+      s[r] = pinned(__builtin_amdgcn_exp2f(s[r]));
+      if (r >= 2) l[r & 1] = pinned(l[r & 1] + s[r - 2]);
+    };
+    f32x16_t sn;
 #pragma unroll
-      for (int t = 0; t < DT; ++t)
+    for (int r = 0; r < 16; ++r) sn[r] = 0.0f;
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) oacc[t][r] *= alpha;
-      m = mnew;
+    for (int u = 0; u < KS; ++u) {
+      sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[u], qf[u], sn, 0, 0, 0);
+      vf[u / DT][u % DT] = fr.tr(Vt, (u / DT) * 16, u % DT);
+#pragma unroll
+      for (int r = 10 * u / KS; r < 10 * (u + 1) / KS; ++r) prob(r);
+      __builtin_amdgcn_sched_barrier(0);
     }
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float p = __builtin_amdgcn_exp2f(s[t][r] - m);
-        s[t][r] = p;
-        l += p;
-      }
-    bf16x8_t pb[4];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) pb[g] = cvt8(s[g >> 1], (g & 1) * 8);
+    pb[0] = cvt8(s, 0);
     // O^T[d][q] += V^T[d][key] P^T[key][q]
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
+    for (int u = 0; u < DT; ++u) {
+      oacc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[0][u], pb[0], oacc[u], 0, 0, 0);
 #pragma unroll
-      for (int g = 0; g < 4; ++g)
-        oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr<LD>(Vt, g * 16, dt * 32, lane), pb[g], oacc[dt],
-                                                           0, 0, 0);
-  };
-
-  if constexpr (kAttnStages == 1 && D <= 96) {
-    // One LDS stage, with K and V on separate schedules: the next block
-    // pair's K tiles are fetched while this pair's softmax and P.V run, and
-    // its V tiles while the next S = K Q^T runs.  Waves 0-1 load the K tiles
-    // and waves 2-3 the V tiles; before a barrier that publishes tiles, only
-    // the waves that loaded them wait for their own loads.  (At d = 128 the
-    // scores held across the middle barrier would cost a wave per SIMD.)
-    auto barrier = [&](bool wait_own_loads) {
-      if (wait_own_loads) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    };
-    load_stage(0, 0);
-    for (int it = 0; it < n_it; ++it) {
-      const int kb = 2 * it + kh, k0 = kb * 64;
-      const bool active = kb < n_kb && k0 <= q0 + 31;
-      f32x16_t s[2];
-      barrier(wave < 2);  // K tiles of this pair landed
-      if (active) scores(smem + kh * TB, s);
-      barrier(wave >= 2);  // every wave is done with the K tiles; V tiles landed
-      if (wave < 2 && it + 1 < n_it) load_stage(it + 1, 0);
-      if (active) softmax_pv(smem + (2 + kh) * TB, k0, s);
-      barrier(false);  // every wave is done with the V tiles
-      if (wave >= 2 && it + 1 < n_it) load_stage(it + 1, 0);
+      for (int r = 10 + 6 * u / DT; r < 10 + 6 * (u + 1) / DT; ++r) prob(r);
+      __builtin_amdgcn_sched_barrier(0);
     }
-  } else {
-    if (kAttnStages == 2) load_stage(0, 0);
-    for (int it = 0; it < n_it; ++it) {
-      const int cur = it % kAttnStages;
-      if (kAttnStages == 1) {
-        __syncthreads();  // every wave is done with the previous block pair
-        load_stage(it, 0);
+    l[0] += s[14];
+    l[1] += s[15];
+    pb[1] = cvt8(s, 8);
+    float mx = sn[0];
+#pragma unroll
+    for (int u = 0; u < DT; ++u) {
+      oacc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[1][u], pb[1], oacc[u], 0, 0, 0);
+      if (u > 0) {
+#pragma unroll
+        for (int r = 1 + 15 * (u - 1) / (DT - 1); r < 1 + 15 * u / (DT - 1); ++r) mx = fmaxf(mx, sn[r]);
+        mx = pinned(mx);
       }
-      __syncthreads();  // this block pair landed (and, with two stages, the other stage is free)
-      if (kAttnStages == 2 && it + 1 < n_it) load_stage(it + 1, (it + 1) % kAttnStages);
-      const int kb = 2 * it + kh, k0 = kb * 64;
-      if (kb >= n_kb || k0 > q0 + 31) continue;
-      f32x16_t s[2];
-      scores(smem + (cur * 4 + kh) * TB, s);
-      softmax_pv(smem + (cur * 4 + 2 + kh) * TB, k0, s);
+      __builtin_amdgcn_sched_barrier(0);
     }
+    s = sn;
+    if (t + 1 == nt - 1) {
+      mask(s, t + 1);
+      mx = s[0];
+#pragma unroll
+      for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
+    }
+    if (t + 1 < nt) new_max(mx);
+  };
+  for (int t = 0; t < nt; t += 2) {
+    step(t, std::integral_constant<int, 0>{});
+    if (t + 1 < nt) step(t + 1, std::integral_constant<int, 1>{});
   }
 
   // Merge the two key halves of each query group (partial m, l, O^T).
   constexpr int XS = 2 + DT * 16;
-  static_assert((size_t)128 * XS * 4 <= (size_t)kAttnStages * 4 * TB, "merge buffer fits the tiles");
+  static_assert((size_t)128 * XS * 4 <= fwd_lds_bytes<D>(), "merge buffer fits the tiles");
   float* xch = reinterpret_cast<float*>(smem) + (size_t)(qg * 64 + lane) * XS;
   __syncthreads();
   if (kh == 1) {
     xch[0] = m;
-    xch[1] = l;
+    xch[1] = l[0] + l[1];
 #pragma unroll
     for (int t = 0; t < DT; ++t)
 #pragma unroll
@@ -314,8 +497,7 @@ __global__ void __launch_bounds__(256) attn_fwd_bf16(int S, int H, int Bm, int m
   const float m1 = xch[0], l1 = xch[1];
   const float mt = fmaxf(m, m1);
   const float a0 = __builtin_amdgcn_exp2f(m - mt), a1 = __builtin_amdgcn_exp2f(m1 - mt);
-  float lt = l * a0 + l1 * a1;
-  lt += __shfl_xor(lt, 32, 64);
+  const float lt = half_sum((l[0] + l[1]) * a0 + l1 * a1);
   const float inv = 1.0f / lt;
   bf16_t* orow = o + ((size_t)b * S + q) * H * D + hh * D;
 #pragma unroll
@@ -792,7 +974,7 @@ __global__ void __launch_bounds__(128) attn_bwd_dkdv_f32(int B, int S, int H, co
 // their launch stubs).
 #define MERAK_ATTN_INST(D)                                                                                        \
   template __global__ void attn_fwd_bf16<D>(int, int, int, int, const bf16_t* __restrict__, bf16_t* __restrict__, \
-                                            float* __restrict__, float);                                         \
+                                            float* __restrict__, float, int, AttnOrder);                         \
   template __global__ void attn_bwd_dkdv_bf16<D>(int, int, int, int, const bf16_t* __restrict__,                 \
                                                  const bf16_t* __restrict__, const float* __restrict__,          \
                                                  const float* __restrict__, bf16_t* __restrict__, float, float); \
@@ -811,18 +993,33 @@ static hipError_t allow_lds(K kern, size_t bytes, std::atomic<uint64_t>& done) {
   return allow_dynamic_lds(reinterpret_cast<const void*>(kern), bytes, done);
 }
 
+// Streamed rows of a (sequence, head) pair: 4 D bytes per token.  A chunk's
+// rows are kept to half of an XCD's 4 MB L2: without chunks, 100 pairs of 2048
+// rows at d = 128 (1 MB each) took 213 us instead of 159 in the forward.  Up to
+// 512 workgroups (two per CU) are resident together, the second half of them
+// beside the first in dispatch order, so there the second half runs shortest
+// first (4 x 8 pairs of 1024 rows: 17.0 -> 16.5 us); larger grids run longest
+// first throughout, which leaves the short blocks for the end.
+static AttnOrder attn_order(int n_pairs, int S, int D) {
+  AttnOrder o;
+  o.n_blk = S / 64;
+  o.chunk = (int)std::max<long long>(1, (2LL << 20) / ((long long)S * D * 4));
+  o.fold = (long long)n_pairs * o.n_blk <= 512;
+  return o;
+}
+
 template <int D>
 static hipError_t fwd_d(int dtype, int B, int S, int H, int G, int mstride, const void* qkv, void* o, float* lse,
                         hipStream_t st) {
   const float scale = 1.0f / sqrtf((float)D);
   if (dtype == DT_BF16) {
-    constexpr size_t lds = attn_lds_bytes<D>();
+    constexpr size_t lds = fwd_lds_bytes<D>();
     static std::atomic<uint64_t> ok{0};
     hipError_t e = allow_lds(attn_fwd_bf16<D>, lds, ok);
     if (e != hipSuccess) return e;
-    dim3 grid(H, G * B, S / 64);
-    hipLaunchKernelGGL((attn_fwd_bf16<D>), grid, dim3(256), lds, st, S, H, B, mstride, (const bf16_t*)qkv,
-                       (bf16_t*)o, lse, scale * kLog2e);
+    const int n_pairs = H * G * B;
+    hipLaunchKernelGGL((attn_fwd_bf16<D>), dim3((unsigned)n_pairs * (S / 64)), dim3(256), lds, st, S, H, B, mstride,
+                       (const bf16_t*)qkv, (bf16_t*)o, lse, scale * kLog2e, n_pairs, attn_order(n_pairs, S, D));
   } else {
     const size_t rs = (size_t)3 * H * D, seq_rows = (size_t)mstride * S;
     for (int m = 0; m < G; ++m) {

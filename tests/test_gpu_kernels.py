@@ -214,6 +214,38 @@ def test_attention_fwd_bwd(dtype, d, seq, batch, heads):
     assert rel_err(g[:, :, 2], dv) < tol
 
 
+# (d, seq, batch, heads): pairs of (sequence, head) below, at and above the eight
+# XCDs' share, with and without leftovers; a grid beyond one resident round; and
+# (the last two) more pairs per XCD than one chunk of the workgroup order holds.
+@pytest.mark.parametrize("d,seq,batch,heads", [(64, 64, 1, 1), (96, 192, 2, 4), (64, 320, 2, 5), (128, 128, 3, 11),
+                                               (96, 1024, 5, 11), (128, 1024, 4, 12)])
+def test_attention_workgroup_order(d, seq, batch, heads):
+    """Every (sequence, head) pair of a large launch equals, bit for bit, the
+    same pair launched alone: the workgroup order covers each row block of each
+    pair exactly once, and no result depends on it."""
+    torch = need_gpu()
+    print(f"[attention order] d={d} seq={seq} batch={batch} heads={heads}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(31 + d + seq)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)  # noqa: E731
+    qkv, do = rnd(batch, seq, 3, heads, d), rnd(batch, seq, heads, d)
+
+    def run(q, g_o, b, h):
+        o = torch.empty((b, seq, h, d), dtype=torch.bfloat16, device="cuda")
+        lse = torch.empty((b, h, seq), dtype=torch.float32, device="cuda")
+        delta, dq = torch.empty_like(lse), torch.empty_like(q)
+        B.attention_fwd(q, o, lse, b, seq, h, d)
+        B.attention_bwd(q, o, lse, g_o, dq, delta, b, seq, h, d)
+        return o, lse, dq
+
+    o, lse, dqkv = run(qkv, do, batch, heads)
+    for b in range(batch):
+        for h in range(heads):
+            o1, l1, d1 = run(qkv[b:b + 1, :, :, h:h + 1].contiguous(), do[b:b + 1, :, h:h + 1].contiguous(), 1, 1)
+            assert torch.equal(o[b, :, h], o1[0, :, 0]) and torch.equal(lse[b, h], l1[0, 0])
+            assert torch.equal(dqkv[b, :, :, h], d1[0, :, :, 0])
+
+
 @pytest.mark.parametrize("cfg", list(range(1, 11)))
 @pytest.mark.parametrize("a_t,b_t", [(0, 0), (0, 1), (1, 1), (1, 0)])
 @pytest.mark.parametrize("K", [64, 192, 320])
