@@ -53,69 +53,6 @@ __device__ __forceinline__ bf16x8_t cvt8(const f32x16_t& a, int base) {
   return __builtin_convertvector(v, bf16x8_t);
 }
 
-// A [64 rows][D] bf16 tile in LDS with rows padded to LD elements: 16-byte
-// reads of 16 consecutive rows hit distinct banks, the transposing reads of 4
-// consecutive rows at most two-way.  LD * 2 is a multiple of 16, so the tile is
-// exactly CPR wave-instructions of 16-byte-per-lane direct loads.
-template <int D>
-struct AttnTile {
-  static constexpr int LD = D == 128 ? D + 24 : D + 8;
-  static constexpr int CPR = LD / 8;         // 16-byte chunks per padded row
-  static constexpr int DC = D / 8;           // data chunks per row
-  static constexpr int BYTES = 64 * LD * 2;  // = CPR * 1024
-};
-
-// One wave's plan for copying rows 0..63 of a tensor (row stride gs
-// elements) into the padded tile with loads that write LDS directly: lane i of
-// instruction q fills chunk 64 q + i (padding chunks re-read a data chunk).
-// The per-lane element offsets are computed once.
-template <int D>
-struct TileLoad {
-  using TT = AttnTile<D>;
-  uint32_t off[TT::CPR];
-  __device__ __forceinline__ void init(size_t gs, int lane) {
-#pragma unroll
-    for (int q = 0; q < TT::CPR; ++q) {
-      const int c = q * 64 + lane;
-      const int row = c / TT::CPR, ch = c % TT::CPR;
-      off[q] = (uint32_t)(row * gs) + (uint32_t)(ch < TT::DC ? ch : 0) * 8u;
-    }
-  }
-  __device__ __forceinline__ void issue(char* lds, const bf16_t* src) const {
-#pragma unroll
-    for (int q = 0; q < TT::CPR; ++q)
-      __builtin_amdgcn_global_load_lds(src + off[q], (MERAK_LDS void*)(lds + q * 1024), 16, 0, 0);
-  }
-};
-
-// 64 floats (one per lane) into LDS with a direct load.
-__device__ __forceinline__ void wave_vec_load(char* lds, const float* src, int lane) {
-  __builtin_amdgcn_global_load_lds(src + lane, (MERAK_LDS void*)lds, 4, 0, 0);
-}
-
-// 8 consecutive elements of row `row` from column `col` of a padded tile.
-template <int LD>
-__device__ __forceinline__ bf16x8_t frag_row(const char* tile, int row, int col) {
-  return *reinterpret_cast<const bf16x8_t*>(tile + (row * LD + col) * 2);
-}
-
-// MFMA operand of X^T taken from a natural tile X[row][col]: lane l gets
-// column col0 + l % 32 and rows kb + 4 (l / 32) + 0..3 (elements 0..3) and
-// kb + 8 + 4 (l / 32) + 0..3 (elements 4..7), the key order of an accumulator
-// reused as the 16-deep operand.  Two transposing LDS reads: in each 16-lane
-// group, lane j fetches 4 columns of row (j / 4) and lane i receives column i of
-// the 4 rows.
-template <int LD>
-__device__ __forceinline__ bf16x8_t frag_tr(const char* tile, int kb, int col0, int lane) {
-  const int row = kb + (lane >> 5) * 4 + ((lane & 15) >> 2);
-  const int col = col0 + ((lane >> 4) & 1) * 16 + (lane & 3) * 4;
-  const char* p = tile + (row * LD + col) * 2;
-  const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((MERAK_LDS s16x4_t*)p);
-  const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((MERAK_LDS s16x4_t*)(p + 8 * LD * 2));
-  const s16x8_t v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-  return __builtin_bit_cast(bf16x8_t, v);
-}
-
 __device__ __forceinline__ bf16x8_t frag_kc(const bf16_t* p) { return *reinterpret_cast<const bf16x8_t*>(p); }
 
 // Sequence index of launch batch z when a launch covers several members (for
@@ -158,19 +95,6 @@ __device__ __forceinline__ AttnSlot attn_slot(int id, int H, int n_pairs, const 
   if (ord.fold && blk >= half) blk = ord.n_blk - 1 - (blk - half);
   return {pair / H, pair % H, blk};
 }
-
-// LDS stages of the bf16 kernels (each four tiles: two 64-row blocks of two
-// tensors).  One stage keeps a workgroup small enough (53 KB at d = 96) to share
-// a CU with a GEMM workgroup of the other stream; the loads of the next block
-// pair are then issued after the current pair has been used.
-#ifndef MERAK_ATTN_STAGES
-#define MERAK_ATTN_STAGES 1
-#endif
-constexpr int kAttnStages = MERAK_ATTN_STAGES;
-static_assert(kAttnStages == 1 || kAttnStages == 2, "one or two LDS stages");
-
-template <int D>
-constexpr size_t attn_lds_bytes() { return (size_t)kAttnStages * 4 * AttnTile<D>::BYTES; }
 
 // ---------------------------------------------------------------------------
 // 32-row tiles for the streaming operands.  A [32 rows][D] bf16 tile is stored
@@ -544,198 +468,230 @@ __global__ void __launch_bounds__(256) attn_delta_kernel(int B, int S, int H, in
 // ---------------------------------------------------------------------------
 // bf16 backward: dK, dV (KV-parallel).  A workgroup owns 64 keys of one
 // (batch, head); wave w takes the 32 keys of group w % 2 against the even
-// (w < 2) or odd 64-query blocks from the diagonal on, and the two partial sums
-// are added at the end.  Each stage holds the Q and dO tiles (and lse, delta)
-// of two query blocks.  P is rebuilt from lse.
+// (w < 2) or odd 32-query tiles from the diagonal on; the two partial sums are
+// added at the end.  Q and dO tiles sit in two-slot rings, loaded one step
+// ahead, with one barrier per step.  P is rebuilt from lse.  Within a step the
+// MFMAs run back to back: S, then dP beside the exponentials of P, then
+// dV += dO^T P beside dS = P (dP - delta), then dK += Q^T dS; each product's
+// fragments are read beside the one before it.  What bounds it: the chain of
+// steps of the first key block (about 3300 cycles each at d = 128, 1024 of them
+// MFMAs), at one (d = 128: 256 registers and 72 accumulation registers) or two
+// workgroups per CU.  Against 64-query blocks loaded after a barrier and used
+// after the next: 2 x 2048 x 6 heads of 128 67.9 -> 53.5 us, 4 x 1024 x 8 of 96
+// 34.2 -> 24.4 us.
 // ---------------------------------------------------------------------------
 template <int D>
-__global__ void __launch_bounds__(256) attn_bwd_dkdv_bf16(int S, int H, int Bm, int mstride,
-                                                          const bf16_t* __restrict__ qkv,
-                                                          const bf16_t* __restrict__ dout,
-                                                          const float* __restrict__ lse,
-                                                          const float* __restrict__ delta,
-                                                          bf16_t* __restrict__ dqkv, float scale_log2,
-                                                          float scale) {
-  using TT = AttnTile<D>;
-  constexpr int LD = TT::LD, KS = D / 16, DT = D / 32, TB = TT::BYTES;
-  extern __shared__ __align__(16) char smem[];  // [stage][Q a, Q b, dO a, dO b], then lse/delta
-  float* vecs = reinterpret_cast<float*>(smem + kAttnStages * 4 * TB);  // [stage][lse a|b, delta a|b]
+constexpr size_t bwd_lds_bytes() { return (size_t)8 * SwTile<D>::BYTES + 2 * 2 * 64 * sizeof(float); }
 
-  // Grid (heads, sequences, key blocks), key block slowest: early keys see the
-  // most queries, so the whole grid runs longest columns first.
-  const int b = seq_index(blockIdx.y, Bm, mstride), hh = blockIdx.x;
-  const int kt = blockIdx.z;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
+template <int D>
+__global__ void __launch_bounds__(256, (D <= 96 ? 2 : 1))
+    attn_bwd_dkdv_bf16(int S, int H, int Bm, int mstride, const bf16_t* __restrict__ qkv,
+                       const bf16_t* __restrict__ dout, const float* __restrict__ lse,
+                       const float* __restrict__ delta, bf16_t* __restrict__ dqkv, float scale_log2, float scale,
+                       int n_pairs, AttnOrder ord) {
+  using ST = SwTile<D>;
+  constexpr int KS = D / 16, DT = D / 32, TB = ST::BYTES;
+  extern __shared__ __align__(16) char smem[];  // [slot][Q even, Q odd, dO even, dO odd], then lse/delta
+  float* const vecs = reinterpret_cast<float*>(smem + 8 * TB);  // [slot][half][lse 32, delta 32]
+
+  const AttnSlot slot = attn_slot(blockIdx.x, H, n_pairs, ord);
+  const int b = seq_index(slot.z, Bm, mstride), hh = slot.hh;
+  const int kt = slot.blk;  // early keys see the most queries
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kg = wave & 1, qh = wave >> 1;
-  const int kw0 = kt * 64 + kg * 32;
-  const int key = kw0 + l32;
+  const int key = kt * 64 + kg * 32 + l32;
   const size_t rs = (size_t)3 * H * D;
   const size_t ors = (size_t)H * D;
   const bf16_t* base = qkv + (size_t)b * S * rs;
-  const bf16_t* Qp = base + hh * D;
   const bf16_t* Kp = base + (size_t)H * D + hh * D;
   const bf16_t* Vp = base + (size_t)2 * H * D + hh * D;
-  const bf16_t* dOp = dout + (size_t)b * S * ors + hh * D;
-  const float* lse_p = lse + ((size_t)b * H + hh) * S;
-  const float* del_p = delta + ((size_t)b * H + hh) * S;
 
+  // Wave w loads tile w of a step (Q or dO of the even or odd queries) and the
+  // 32 lse or delta values that go with it; the values pass through a register,
+  // fetched a step before they are written to LDS.  lse is staged in log2 units.
+  const int nt = S / 64 - kt;  // steps; tile t of half q holds queries 64 (kt + t) + 32 q ..
+  const bool is_do = wave >= 2;
+  const size_t lgs = is_do ? ors : rs;
+  const bf16_t* lsrc = (is_do ? dout + (size_t)b * S * ors : base) + hh * D + (size_t)(kt * 64 + (wave & 1) * 32) * lgs;
+  const float* vsrc = (is_do ? delta : lse) + ((size_t)b * H + hh) * S + kt * 64 + (wave & 1) * 32 + l32;
+  const float vscale = is_do ? 1.0f : kLog2e;
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(MERAK_LDS char*)smem) + wave * TB;
+  float* const vdst = vecs + (wave & 1) * 64 + (is_do ? 32 : 0) + l32;
+  TileDma<D> dma;
+  dma.init(lgs, lane);
+  auto load = [&](int t) {
+    if (t < nt) dma.issue(lds0 + (t & 1) * 4 * TB, lsrc + (size_t)t * 64 * lgs);
+  };
+  TileFrag<D> fr;
+  fr.init(lane);
   bf16x8_t kf[KS], vf[KS];
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) {
     kf[ks] = frag_kc(Kp + (size_t)key * rs + ks * 16 + hf * 8);
     vf[ks] = frag_kc(Vp + (size_t)key * rs + ks * 16 + hf * 8);
   }
+  float vnext = vsrc[0];
+  load(0);
+  // The wait for these loads belongs here: left to their first use it would
+  // also cover later tile loads.
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(kf[ks]), "+v"(vf[ks]));
+  vdst[0] = vnext * vscale;
+  if (nt > 1) vnext = vsrc[64];
+
   f32x16_t dk[DT], dv[DT];
 #pragma unroll
   for (int t = 0; t < DT; ++t)
 #pragma unroll
     for (int r = 0; r < 16; ++r) dk[t][r] = dv[t][r] = 0.0f;
 
-  const int n_qb = S / 64 - kt;  // query blocks kt .. S/64-1
-  const int n_it = (n_qb + 1) / 2;
-  const bool is_do = (wave >> 1) != 0;
-  const size_t lgs = is_do ? ors : rs;
-  TileLoad<D> tl;
-  tl.init(lgs, lane);
-  const bf16_t* lsrc = is_do ? dOp : Qp;
-  const float* vsrc = is_do ? del_p : lse_p;
-  auto load_stage = [&](int it, int stage) {
-    const int blk = kt + 2 * it + (wave & 1);
-    if (2 * it + (wave & 1) < n_qb) {
-      tl.issue(smem + (stage * 4 + wave) * TB, lsrc + (size_t)blk * 64 * lgs);
-      float* v = vecs + stage * 256 + (wave & 1) * 64 + (is_do ? 128 : 0);
-      if (is_do) wave_vec_load(reinterpret_cast<char*>(v), vsrc + (size_t)blk * 64, lane);
-      else v[lane] = vsrc[(size_t)blk * 64 + lane] * kLog2e;  // lse staged in log2 units
+  auto step = [&](int t, auto slot_c) {
+    constexpr int SLOT = decltype(slot_c)::value;
+    step_barrier();  // this step's tiles are there; those of the step before are no longer needed
+    if (t + 1 < nt) {
+      vdst[(SLOT ^ 1) * 128] = vnext * vscale;
+      if (t + 2 < nt) vnext = vsrc[(size_t)(t + 2) * 64];
     }
+    load(t + 1);
+    const char* Qt = smem + (SLOT * 4 + qh) * TB;
+    const char* dOt = smem + (SLOT * 4 + 2 + qh) * TB;
+    const float* vec = vecs + SLOT * 128 + qh * 64 + hf * 4;
+    f32x16_t p, dp;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) p[r] = dp[r] = 0.0f;
+    // Each product's fragments are read while the one before it runs.
+    static_assert(KS == 2 * DT, "as many row fragments as transposed ones");
+    bf16x8_t fa[KS], fb[KS];
+    f32x4_t ls[4], de[4];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) fa[ks] = fr.row(Qt, ks);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) ls[g] = *reinterpret_cast<const f32x4_t*>(vec + g * 8);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      p = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks], kf[ks], p, 0, 0, 0);
+      fb[ks] = fr.row(dOt, ks);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // p[r]: query 64 (kt + t) + 32 qh + (r/4)*8 + 4*hf + r%4, key `key`.
+    if (t == 0) {  // the only tiles with queries before a key
+      const int lim = key - (kt * 64 + qh * 32) - hf * 4;
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if ((r >> 2) * 8 + (r & 3) < lim) p[r] = -INFINITY;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[ks], vf[ks], dp, 0, 0, 0);
+      fa[ks] = fr.tr(dOt, (ks / DT) * 16, ks % DT);
+#pragma unroll
+      for (int r = 16 * ks / KS; r < 16 * (ks + 1) / KS; ++r)
+        p[r] = pinned(__builtin_amdgcn_exp2f(fmaf(p[r], scale_log2, -ls[r >> 2][r & 3])));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    const bf16x8_t pb[2] = {cvt8(p, 0), cvt8(p, 8)};
+#pragma unroll
+    for (int g = 0; g < 4; ++g) de[g] = *reinterpret_cast<const f32x4_t*>(vec + 32 + g * 8);
+    // dV^T[d][key] += dO^T[d][q] P[q][key];  dK^T[d][key] += Q^T[d][q] dS[q][key]
+#pragma unroll
+    for (int u = 0; u < KS; ++u) {
+      dv[u % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[u], pb[u / DT], dv[u % DT], 0, 0, 0);
+      fb[u] = fr.tr(Qt, (u / DT) * 16, u % DT);
+#pragma unroll
+      for (int r = 16 * u / KS; r < 16 * (u + 1) / KS; ++r) p[r] = pinned(p[r] * (dp[r] - de[r >> 2][r & 3]));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    const bf16x8_t sb[2] = {cvt8(p, 0), cvt8(p, 8)};
+#pragma unroll
+    for (int u = 0; u < KS; ++u)
+      dk[u % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[u], sb[u / DT], dk[u % DT], 0, 0, 0);
   };
-
-  if (kAttnStages == 2) load_stage(0, 0);
-  for (int it = 0; it < n_it; ++it) {
-    const int cur = it % kAttnStages;
-    if (kAttnStages == 1) {
-      __syncthreads();
-      load_stage(it, 0);
-    }
-    __syncthreads();
-    if (kAttnStages == 2 && it + 1 < n_it) load_stage(it + 1, (it + 1) % kAttnStages);
-    const int qb = kt + 2 * it + qh, qs = qb * 64;
-    if (2 * it + qh >= n_qb || qs + 63 < kw0) continue;
-    const char* Qt = smem + (cur * 4 + qh) * TB;
-    const char* dOt = smem + (cur * 4 + 2 + qh) * TB;
-    const float* lse_s = vecs + cur * 256 + qh * 64;
-    const float* del_s = lse_s + 128;
-
-    // The two 32-query halves of the block one after the other (smaller live
-    // register set); each dK/dV accumulator still takes its four 16-query
-    // groups in order 0..3, so the sums are those of the whole block.
-    const bool diag = qs < kw0 + 32;  // some query of the block precedes some key of the wave
-    // Query qs + qi precedes this lane's key iff qi < key - qs.  With the lane's
-    // part of qi (4 hf) folded in, one compare against a constant per score
-    // decides; off the diagonal the limit is below every qi and masks nothing.
-    const int mlim = (diag ? key - qs : -1) - hf * 4;
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      f32x16_t p, dp;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) p[r] = dp[r] = 0.0f;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        p = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_row<LD>(Qt, t * 32 + l32, ks * 16 + hf * 8), kf[ks], p, 0,
-                                                    0, 0);
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_row<LD>(dOt, t * 32 + l32, ks * 16 + hf * 8), vf[ks], dp,
-                                                     0, 0, 0);
-      }
-      // p[r]: query qs + t*32 + (r/4)*8 + 4*hf + r%4, key `key`.
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int qc = t * 32 + (r >> 2) * 8 + (r & 3);
-        const int qi = qc + hf * 4;
-        float pv = __builtin_amdgcn_exp2f(fmaf(p[r], scale_log2, -lse_s[qi]));
-        if (qc < mlim) pv = 0.0f;
-        p[r] = pv;
-        dp[r] = pv * (dp[r] - del_s[qi]);
-      }
-      const bf16x8_t pb[2] = {cvt8(p, 0), cvt8(p, 8)};
-      const bf16x8_t sb[2] = {cvt8(dp, 0), cvt8(dp, 8)};
-      // dV^T[d][key] += dO^T[d][q] P[q][key];  dK^T[d][key] += Q^T[d][q] dS[q][key]
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int gg = 0; gg < 2; ++gg) {
-          const int g = 2 * t + gg;
-          dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr<LD>(dOt, g * 16, dt * 32, lane), pb[gg], dv[dt],
-                                                           0, 0, 0);
-          dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr<LD>(Qt, g * 16, dt * 32, lane), sb[gg], dk[dt],
-                                                           0, 0, 0);
-        }
-    }
+  for (int t = 0; t < nt; t += 2) {
+    step(t, std::integral_constant<int, 0>{});
+    if (t + 1 < nt) step(t + 1, std::integral_constant<int, 1>{});
   }
 
-  // Add the two query halves.
-  constexpr int XS = 2 * DT * 16;
-  static_assert((size_t)128 * XS * 4 <= (size_t)kAttnStages * 4 * TB, "merge buffer fits the tiles");
-  float* xch = reinterpret_cast<float*>(smem) + (size_t)(kg * 64 + lane) * XS;
-  __syncthreads();
-  if (qh == 1) {
+  // Add the two query halves: the even half's waves finish dK, the odd half's
+  // dV, each handing over the other.
+  static_assert((size_t)4 * DT * 4096 <= (size_t)8 * TB, "merge buffer fits the tiles");
+  char* const mine = smem + (kg * 2 + qh) * DT * 4096 + lane * 16;
+  const char* const theirs = smem + (kg * 2 + (qh ^ 1)) * DT * 4096 + lane * 16;
+  auto put = [&](const f32x16_t (&a)[DT]) {
 #pragma unroll
     for (int t = 0; t < DT; ++t)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        xch[t * 16 + r] = dk[t][r];
-        xch[DT * 16 + t * 16 + r] = dv[t][r];
+      for (int i = 0; i < 4; ++i)
+        *reinterpret_cast<f32x4_t*>(mine + (t * 4 + i) * 1024) =
+            f32x4_t{a[t][4 * i], a[t][4 * i + 1], a[t][4 * i + 2], a[t][4 * i + 3]};
+  };
+  auto finish = [&](const f32x16_t (&a)[DT], bf16_t* row, float f) {
+#pragma unroll
+    for (int t = 0; t < DT; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const f32x4_t o = *reinterpret_cast<const f32x4_t*>(theirs + (t * 4 + i) * 1024);
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = (a[t][4 * i + e] + o[e]) * f;
+        store4(row + t * 32 + i * 8 + hf * 4, v);
       }
-  }
+  };
   __syncthreads();
-  if (qh == 1) return;
+  if (qh == 0) put(dv);
+  else put(dk);
+  __syncthreads();
   bf16_t* krow = dqkv + ((size_t)b * S + key) * rs + (size_t)H * D + hh * D;
-  bf16_t* vrow = krow + (size_t)H * D;
-#pragma unroll
-  for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      float a[4], c[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        a[e] = (dk[dt][4 * g + e] + xch[dt * 16 + 4 * g + e]) * scale;
-        c[e] = dv[dt][4 * g + e] + xch[DT * 16 + dt * 16 + 4 * g + e];
-      }
-      store4(krow + dt * 32 + g * 8 + hf * 4, a);
-      store4(vrow + dt * 32 + g * 8 + hf * 4, c);
-    }
+  if (qh == 0) finish(dk, krow, scale);
+  else finish(dv, krow + (size_t)H * D, 1.0f);
 }
 
 // ---------------------------------------------------------------------------
 // bf16 backward: dQ (Q-parallel), the forward's layout: 64 query rows per
-// workgroup, 2 query groups x 2 key halves, K and V tiles of two key blocks per
-// stage, partial dQ sums added at the end.  It also writes delta for its rows,
-// which the dK/dV kernel launched after it reads.
+// workgroup, 2 query groups x even / odd 32-key tiles, K and V tiles in two-slot
+// rings, partial dQ sums added at the end.  It also writes delta for its rows,
+// which the dK/dV kernel launched after it reads.  229 registers at d = 128 keep
+// two workgroups per CU (one before): 2 x 2048 x 6 heads of 128 51.6 -> 36.2 us;
+// 4 x 1024 x 8 of 96 25.2 -> 21.6 us.
 // ---------------------------------------------------------------------------
 template <int D>
-__global__ void __launch_bounds__(256) attn_bwd_dq_bf16(int S, int H, int Bm, int mstride,
-                                                        const bf16_t* __restrict__ qkv,
-                                                        const bf16_t* __restrict__ o,
-                                                        const bf16_t* __restrict__ dout,
-                                                        const float* __restrict__ lse,
-                                                        float* __restrict__ delta,
-                                                        bf16_t* __restrict__ dqkv, float scale_log2, float scale) {
-  using TT = AttnTile<D>;
-  constexpr int LD = TT::LD, KS = D / 16, DT = D / 32, TB = TT::BYTES;
-  extern __shared__ __align__(16) char smem[];
+__global__ void __launch_bounds__(256, 2) attn_bwd_dq_bf16(int S, int H, int Bm, int mstride,
+                                                           const bf16_t* __restrict__ qkv,
+                                                           const bf16_t* __restrict__ o,
+                                                           const bf16_t* __restrict__ dout,
+                                                           const float* __restrict__ lse, float* __restrict__ delta,
+                                                           bf16_t* __restrict__ dqkv, float scale_log2, float scale,
+                                                           int n_pairs, AttnOrder ord) {
+  using ST = SwTile<D>;
+  constexpr int KS = D / 16, DT = D / 32, TB = ST::BYTES;
+  extern __shared__ __align__(16) char smem[];  // [slot][K even, K odd, V even, V odd]
 
-  const int b = seq_index(blockIdx.y, Bm, mstride), hh = blockIdx.x;  // grid as in the forward
-  const int qt = gridDim.z - 1 - blockIdx.z;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
+  const AttnSlot slot = attn_slot(blockIdx.x, H, n_pairs, ord);
+  const int b = seq_index(slot.z, Bm, mstride), hh = slot.hh;
+  const int qt = ord.n_blk - 1 - slot.blk;
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qg = wave & 1, kh = wave >> 1;
-  const int q0 = qt * 64 + qg * 32;
-  const int q = q0 + l32;
+  const int q = qt * 64 + qg * 32 + l32;
   const size_t rs = (size_t)3 * H * D;
   const size_t ors = (size_t)H * D;
   const bf16_t* base = qkv + (size_t)b * S * rs;
   const bf16_t* Qp = base + hh * D;
-  const bf16_t* Kp = base + (size_t)H * D + hh * D;
-  const bf16_t* Vp = base + (size_t)2 * H * D + hh * D;
   const bf16_t* dOp = dout + (size_t)b * S * ors + hh * D;
 
+  const int nt = qt + 1;  // steps; tile t of half kh holds keys 64 t + 32 kh ..
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(MERAK_LDS char*)smem) + wave * TB;
+  const bf16_t* lsrc = base + (size_t)(1 + kh) * H * D + hh * D + (size_t)(wave & 1) * 32 * rs;
+  TileDma<D> dma;
+  dma.init(rs, lane);
+  auto load = [&](int t) {
+    if (t < nt) dma.issue(lds0 + (t & 1) * 4 * TB, lsrc + (size_t)t * 64 * rs);
+  };
+  TileFrag<D> fr;
+  fr.init(lane);
+  load(0);
   bf16x8_t qf[KS], of[KS];
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) {
@@ -754,103 +710,110 @@ __global__ void __launch_bounds__(256) attn_bwd_dq_bf16(int S, int H, int Bm, in
     for (int ks = 0; ks < KS; ++ks) {
       float ov[8], dv[8];
       load8(Op + (size_t)q * ors + ks * 16 + hf * 8, ov);
-      load8(dOp + (size_t)q * ors + ks * 16 + hf * 8, dv);
+      unpack8(__builtin_bit_cast(u32x4_t, of[ks]), dv);
 #pragma unroll
       for (int e = 0; e < 8; ++e) part += dv[e] * ov[e];
     }
-    del = part + __shfl_xor(part, 32, 64);
+    del = half_sum(part);
     if (kh == 0 && hf == 0) delta[((size_t)b * H + hh) * S + q] = del;
   }
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qf[ks]), "+v"(of[ks]));
   f32x16_t dq[DT];
 #pragma unroll
   for (int t = 0; t < DT; ++t)
 #pragma unroll
     for (int r = 0; r < 16; ++r) dq[t][r] = 0.0f;
 
-  const int n_kb = qt + 1;
-  const int n_it = (n_kb + 1) / 2;
-  TileLoad<D> tl;
-  tl.init(rs, lane);
-  const bf16_t* lsrc = (wave >> 1) ? Vp : Kp;
-  auto load_stage = [&](int it, int stage) {
-    const int blk = 2 * it + (wave & 1);
-    if (blk < n_kb) tl.issue(smem + (stage * 4 + wave) * TB, lsrc + (size_t)blk * 64 * rs);
-  };
-
-  if (kAttnStages == 2) load_stage(0, 0);
-  for (int it = 0; it < n_it; ++it) {
-    const int cur = it % kAttnStages;
-    if (kAttnStages == 1) {
-      __syncthreads();
-      load_stage(it, 0);
+  auto step = [&](int t, auto slot_c) {
+    constexpr int SLOT = decltype(slot_c)::value;
+    step_barrier();  // this step's tiles are there; those of the step before are no longer needed
+    load(t + 1);
+    const char* Kt = smem + (SLOT * 4 + kh) * TB;
+    const char* Vt = smem + (SLOT * 4 + 2 + kh) * TB;
+    f32x16_t p, dp;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) p[r] = dp[r] = 0.0f;
+    // Each product's fragments are read while the one before it runs.
+    static_assert(KS == 2 * DT, "as many row fragments as transposed ones");
+    bf16x8_t fa[KS], fb[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) fa[ks] = fr.row(Kt, ks);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      p = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks], qf[ks], p, 0, 0, 0);
+      fb[ks] = fr.row(Vt, ks);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    __syncthreads();
-    if (kAttnStages == 2 && it + 1 < n_it) load_stage(it + 1, (it + 1) % kAttnStages);
-    const int kb = 2 * it + kh, k0 = kb * 64;
-    if (kb >= n_kb || k0 > q0 + 31) continue;
-    const char* Kt = smem + (cur * 4 + kh) * TB;
-    const char* Vt = smem + (cur * 4 + 2 + kh) * TB;
-    f32x16_t p[2], dp[2];
+    // p[r]: key 64 t + 32 kh + (r/4)*8 + 4*hf + r%4, query q.
+    if (t == nt - 1) {  // the only tiles that reach past a query
+      const int lim = q - (64 * t + 32 * kh) - hf * 4;
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) p[t][r] = dp[t][r] = 0.0f;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        p[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_row<LD>(Kt, t * 32 + l32, ks * 16 + hf * 8), qf[ks], p[t],
-                                                       0, 0, 0);
-        dp[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_row<LD>(Vt, t * 32 + l32, ks * 16 + hf * 8), of[ks],
-                                                        dp[t], 0, 0, 0);
-      }
+      for (int r = 0; r < 16; ++r)
+        if ((r >> 2) * 8 + (r & 3) > lim) p[r] = -INFINITY;
     }
-    // the causal mask only on a block that reaches past the wave's first query
-    auto probs = [&](auto diag_c) {
-      constexpr bool DIAG = decltype(diag_c)::value;
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
+    for (int ks = 0; ks < KS; ++ks) {
+      dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[ks], of[ks], dp, 0, 0, 0);
+      fa[ks] = fr.tr(Kt, (ks / DT) * 16, ks % DT);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int kk = k0 + t * 32 + (r >> 2) * 8 + hf * 4 + (r & 3);
-          float pv = __builtin_amdgcn_exp2f(fmaf(p[t][r], scale_log2, -lse2));
-          if (DIAG && kk > q) pv = 0.0f;
-          dp[t][r] = pv * (dp[t][r] - del);
-        }
-    };
-    if (k0 + 63 > q0) probs(std::true_type{});
-    else probs(std::false_type{});
-    bf16x8_t sb[4];
+      for (int r = 16 * ks / KS; r < 16 * (ks + 1) / KS; ++r)
+        p[r] = pinned(__builtin_amdgcn_exp2f(fmaf(p[r], scale_log2, -lse2)));
+      __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll
-    for (int g = 0; g < 4; ++g) sb[g] = cvt8(dp[g >> 1], (g & 1) * 8);
+    for (int r = 0; r < 16; ++r) p[r] *= dp[r] - del;
+    const bf16x8_t sb[2] = {cvt8(p, 0), cvt8(p, 8)};
     // dQ^T[d][q] += K^T[d][key] dS^T[key][q]
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-      for (int g = 0; g < 4; ++g)
-        dq[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr<LD>(Kt, g * 16, dt * 32, lane), sb[g], dq[dt], 0, 0, 0);
+    for (int u = 0; u < KS; ++u)
+      dq[u % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[u], sb[u / DT], dq[u % DT], 0, 0, 0);
+  };
+  for (int t = 0; t < nt; t += 2) {
+    step(t, std::integral_constant<int, 0>{});
+    if (t + 1 < nt) step(t + 1, std::integral_constant<int, 1>{});
   }
 
-  constexpr int XS = DT * 16;
-  static_assert((size_t)128 * XS * 4 <= (size_t)kAttnStages * 4 * TB, "merge buffer fits the tiles");
-  float* xch = reinterpret_cast<float*>(smem) + (size_t)(qg * 64 + lane) * XS;
-  __syncthreads();
-  if (kh == 1) {
+  // Add the two key halves; each finishes half of the columns.
+  constexpr int DH = (DT + 1) / 2;  // 32-column groups finished by the even half
+  static_assert((size_t)4 * DH * 4096 <= (size_t)8 * TB, "merge buffer fits the tiles");
+  char* const mine = smem + (qg * 2 + kh) * DH * 4096 + lane * 16;
+  const char* const theirs = smem + (qg * 2 + (kh ^ 1)) * DH * 4096 + lane * 16;
+  auto put = [&](int dt, int at) {
 #pragma unroll
-    for (int t = 0; t < DT; ++t)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) xch[t * 16 + r] = dq[t][r];
-  }
-  __syncthreads();
-  if (kh == 1) return;
+    for (int i = 0; i < 4; ++i)
+      *reinterpret_cast<f32x4_t*>(mine + (at * 4 + i) * 1024) =
+          f32x4_t{dq[dt][4 * i], dq[dt][4 * i + 1], dq[dt][4 * i + 2], dq[dt][4 * i + 3]};
+  };
   bf16_t* qrow = dqkv + ((size_t)b * S + q) * rs + hh * D;
+  auto finish = [&](int dt, int at) {
 #pragma unroll
-  for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
+    for (int i = 0; i < 4; ++i) {
+      const f32x4_t x = *reinterpret_cast<const f32x4_t*>(theirs + (at * 4 + i) * 1024);
       float a[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) a[e] = (dq[dt][4 * g + e] + xch[dt * 16 + 4 * g + e]) * scale;
-      store4(qrow + dt * 32 + g * 8 + hf * 4, a);
+      for (int e = 0; e < 4; ++e) a[e] = (dq[dt][4 * i + e] + x[e]) * scale;
+      store4(qrow + dt * 32 + i * 8 + hf * 4, a);
     }
+  };
+  __syncthreads();
+  if (kh == 0) {
+#pragma unroll
+    for (int dt = DH; dt < DT; ++dt) put(dt, dt - DH);
+  } else {
+#pragma unroll
+    for (int dt = 0; dt < DH; ++dt) put(dt, dt);
+  }
+  __syncthreads();
+  if (kh == 0) {
+#pragma unroll
+    for (int dt = 0; dt < DH; ++dt) finish(dt, dt);
+  } else {
+#pragma unroll
+    for (int dt = DH; dt < DT; ++dt) finish(dt, dt - DH);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -977,11 +940,12 @@ __global__ void __launch_bounds__(128) attn_bwd_dkdv_f32(int B, int S, int H, co
                                             float* __restrict__, float, int, AttnOrder);                         \
   template __global__ void attn_bwd_dkdv_bf16<D>(int, int, int, int, const bf16_t* __restrict__,                 \
                                                  const bf16_t* __restrict__, const float* __restrict__,          \
-                                                 const float* __restrict__, bf16_t* __restrict__, float, float); \
+                                                 const float* __restrict__, bf16_t* __restrict__, float, float,  \
+                                                 int, AttnOrder);                                                \
   template __global__ void attn_bwd_dq_bf16<D>(int, int, int, int, const bf16_t* __restrict__,                   \
                                                const bf16_t* __restrict__, const bf16_t* __restrict__,           \
                                                const float* __restrict__, float* __restrict__,                   \
-                                               bf16_t* __restrict__, float, float);
+                                               bf16_t* __restrict__, float, float, int, AttnOrder);
 MERAK_ATTN_INST(64)
 MERAK_ATTN_INST(96)
 MERAK_ATTN_INST(128)
@@ -1038,19 +1002,21 @@ static hipError_t bwd_d(int dtype, int B, int S, int H, int G, int mstride, cons
   const float scale = 1.0f / sqrtf((float)D);
   const int rows = G * B * S * H;
   if (dtype == DT_BF16) {
-    constexpr size_t lds_q = attn_lds_bytes<D>();
-    constexpr size_t lds_k = attn_lds_bytes<D>() + kAttnStages * 256 * sizeof(float);
+    constexpr size_t lds_q = fwd_lds_bytes<D>(), lds_k = bwd_lds_bytes<D>();
     static_assert(lds_k <= 160 * 1024, "LDS budget");
     static std::atomic<uint64_t> ok_k{0}, ok_q{0};
     hipError_t e = allow_lds(attn_bwd_dkdv_bf16<D>, lds_k, ok_k);
     if (e == hipSuccess) e = allow_lds(attn_bwd_dq_bf16<D>, lds_q, ok_q);
     if (e != hipSuccess) return e;
     // dQ first: it also forms delta, which dK/dV reads.
-    dim3 grid(H, G * B, S / 64);
+    const int n_pairs = H * G * B;
+    const dim3 grid((unsigned)n_pairs * (S / 64));
+    const AttnOrder ord = attn_order(n_pairs, S, D);
     hipLaunchKernelGGL((attn_bwd_dq_bf16<D>), grid, dim3(256), lds_q, st, S, H, B, mstride, (const bf16_t*)qkv,
-                       (const bf16_t*)o, (const bf16_t*)dout, lse, delta, (bf16_t*)dqkv, scale * kLog2e, scale);
+                       (const bf16_t*)o, (const bf16_t*)dout, lse, delta, (bf16_t*)dqkv, scale * kLog2e, scale,
+                       n_pairs, ord);
     hipLaunchKernelGGL((attn_bwd_dkdv_bf16<D>), grid, dim3(256), lds_k, st, S, H, B, mstride, (const bf16_t*)qkv,
-                       (const bf16_t*)dout, lse, delta, (bf16_t*)dqkv, scale * kLog2e, scale);
+                       (const bf16_t*)dout, lse, delta, (bf16_t*)dqkv, scale * kLog2e, scale, n_pairs, ord);
   } else {
     hipLaunchKernelGGL((attn_delta_kernel<float, D>), dim3((rows + 255) / 256), dim3(256), 0, st, G * B, S, H, B,
                        mstride, (const float*)o, (const float*)dout, delta);
