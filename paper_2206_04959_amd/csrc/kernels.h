@@ -35,9 +35,10 @@ struct GemmProblem {
 constexpr int kMaxGroup = 4;
 
 // Launch 1..kMaxGroup independent problems sharing layout, epilogue and dtype
-// as one grid.
+// as one grid.  `alone`: nothing else runs beside the launch (the tile choice
+// then fills the chip's CUs; otherwise it saves operand traffic).
 hipError_t launch_gemm(int dtype, bool a_t, bool b_t, int epi, const GemmProblem* probs, int n_probs,
-                       hipStream_t stream);
+                       hipStream_t stream, bool alone = false);
 // Whether the bf16 kernel can address both operands of `q`: it uses 32-bit
 // byte offsets, counting the rows of a partial edge tile (up to 256 past M or
 // N).  launch_gemm refuses a problem that does not fit.

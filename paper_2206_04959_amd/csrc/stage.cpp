@@ -1139,7 +1139,7 @@ int merak_gemm(int dtype, int a_trans, int b_trans, int epilogue, int M, int N, 
   if (accumulate != 0 && accumulate != 1) return MERAK_ERR_INVALID_ARG;
   GemmProblem p = gp(M, N, K, a, lda, b, ldb, c, N, bias, resid, aux, accumulate);
   if (dtype == MERAK_BF16 && !gemm_bf16_offsets_fit(p, a_trans, b_trans)) return MERAK_ERR_SHAPE;
-  HIP_TRY(launch_gemm(dtype, a_trans, b_trans, epilogue, &p, 1, (hipStream_t)stream));
+  HIP_TRY(launch_gemm(dtype, a_trans, b_trans, epilogue, &p, 1, (hipStream_t)stream, true));
   return MERAK_OK;
 }
 

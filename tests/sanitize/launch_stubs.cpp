@@ -6,7 +6,7 @@
 
 namespace merak {
 static hipError_t unreachable() { abort(); }
-hipError_t launch_gemm(int, bool, bool, int, const GemmProblem*, int, hipStream_t) { return unreachable(); }
+hipError_t launch_gemm(int, bool, bool, int, const GemmProblem*, int, hipStream_t, bool) { return unreachable(); }
 hipError_t launch_layernorm_fwd(int, int, int, float, const void*, const void*, const void*, void*, float*, float*,
                                 hipStream_t, int, int) { return unreachable(); }
 hipError_t launch_layernorm_bwd(int, int, int, const void*, const void*, const float*, const float*, const void*,

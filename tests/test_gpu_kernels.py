@@ -77,6 +77,27 @@ def test_gemm_smallest_problem_on_every_tile(cfg, a_t, b_t):
     assert rel_err(c32.cpu().numpy(), ref) < 2e-5
 
 
+# (M, N, K) for which the choice for a lone launch is 64x128 (or 128x128 where A
+# is read transposed), 128x128, 192x128, 128x192 and 256x128 tiles, each with
+# ragged last tiles and more K stages than the ring holds; and one K stage.
+@pytest.mark.parametrize("a_t,b_t", [(0, 0), (0, 1), (1, 1), (1, 0)])
+@pytest.mark.parametrize("mnk", [(960, 1088, 320), (1984, 1600, 320), (3008, 1984, 576), (1984, 3008, 576),
+                                 (3840, 1984, 576), (960, 1088, 64), (1984, 1600, 64)])
+def test_gemm_lone_launch_tiles(mnk, a_t, b_t):
+    """fp32 output, so the tolerance is that of fp32 sums of up to 576 products
+    of bf16 values (2e-5 of the largest, as for every tile shape below)."""
+    torch = need_gpu()
+    M, N, K = mnk
+    print(f"[gemm lone] a_t={a_t} b_t={b_t} {mnk}", flush=True)
+    a_p, a = _rand((K, M) if a_t else (M, K), "bf16", 25)
+    b_p, b = _rand((K, N) if b_t else (N, K), "bf16", 26)
+    ref = (a.T if a_t else a) @ (b if b_t else b.T)
+    c32 = torch.empty((M, N), dtype=torch.float32, device="cuda")
+    B.gemm(_dev(a_p), _dev(b_p), c32, M, N, K, a_trans=a_t, b_trans=b_t, epilogue=B.EPI_F32, dtype=B.BF16)
+    torch.cuda.synchronize()
+    assert rel_err(c32.cpu().numpy(), ref) < 2e-5
+
+
 # bf16: the automatic tile choice and each tile the stage's choice can make
 # (256x256, 256x128 and 128x192 tiles, 256x192); fp32 has one kernel.
 EPI_CASES = [("bf16", 0), ("bf16", 7), ("bf16", 8), ("bf16", 9), ("bf16", 10), ("fp32", 0)]
