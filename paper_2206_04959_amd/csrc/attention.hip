@@ -25,7 +25,7 @@
 // mean row (e/4)*8 + (l/32)*4 + e%4 of that 16-row group; the other operand is
 // read with transposing LDS reads in the same key order (two 8-byte reads).
 //
-// fp32 check mode: one thread per query (or key) row, fp32 throughout.
+// fp32 check mode: the same split with fp32 matrix instructions, fp32 throughout.
 #include <math.h>
 #include <algorithm>
 #include <atomic>
@@ -438,34 +438,6 @@ __global__ void __launch_bounds__(256, 2) attn_fwd_bf16(int S, int H, int Bm, in
 }
 
 // ---------------------------------------------------------------------------
-// delta[b, h, i] = sum_d dO[b, i, h, d] * O[b, i, h, d] (fp32 check mode; the
-// bf16 dQ kernel forms it itself)
-// ---------------------------------------------------------------------------
-template <typename T, int D>
-__global__ void __launch_bounds__(256) attn_delta_kernel(int B, int S, int H, int Bm, int mstride,
-                                                         const T* __restrict__ o, const T* __restrict__ dout,
-                                                         float* __restrict__ delta) {
-  const int row = blockIdx.x * 256 + threadIdx.x;  // (launch batch, i, h) flattened
-  if (row >= B * S * H) return;
-  const int hh = row % H;
-  const int bi = row / H;
-  const int i = bi % S, b = seq_index(bi / S, Bm, mstride);
-  const size_t trow = ((size_t)b * S + i) * H + hh;
-  const T* orow = o + trow * D;
-  const T* drow = dout + trow * D;
-  float s = 0.0f;
-#pragma unroll
-  for (int c = 0; c < D; c += 8) {
-    float a[8], d[8];
-    load8(orow + c, a);
-    load8(drow + c, d);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) s += a[e] * d[e];
-  }
-  delta[((size_t)b * H + hh) * S + i] = s;
-}
-
-// ---------------------------------------------------------------------------
 // bf16 backward: dK, dV (KV-parallel).  A workgroup owns 64 keys of one
 // (batch, head); wave w takes the 32 keys of group w % 2 against the even
 // (w < 2) or odd 32-query tiles from the diagonal on; the two partial sums are
@@ -817,117 +789,239 @@ __global__ void __launch_bounds__(256, 2) attn_bwd_dq_bf16(int S, int H, int Bm,
 }
 
 // ---------------------------------------------------------------------------
-// fp32 check mode
+// fp32 check mode, on the fp32 matrix instruction (v_mfma_f32_32x32x2_f32: fp32
+// products and sums).  A workgroup owns 32 rows of one (batch, head); each of
+// its four waves takes every fourth 32-row tile of the other sequence axis, and
+// the four partial results are merged at the end in wave order.  Operands come
+// straight from global memory: the 32x32x2 product's k index h of its step j
+// of chunk c is taken to mean column 8 c + 4 h + j (h = lane / 32), so a lane
+// reads 16 bytes of its row; products over the tile's rows take an accumulator
+// register as one operand (rows (r/4)*8 + 4 h + r%4) and one row segment of 32
+// columns as the other.  What bounds it: small calls are a chain of a few
+// tiles (a tile is 2 x 4096 cycles of MFMAs at d = 128).  One thread per row,
+// as before, took 221 + 422 us forward and backward at 2 x 128 x 4 heads of 64.
 // ---------------------------------------------------------------------------
 template <int D>
-__global__ void __launch_bounds__(128) attn_fwd_f32(int B, int S, int H, const float* __restrict__ qkv,
-                                                    float* __restrict__ o, float* __restrict__ lse, float scale) {
-  const int idx = blockIdx.x * 128 + threadIdx.x;  // (b, h, i), i fastest
-  if (idx >= B * H * S) return;
-  const int i = idx % S, hh = (idx / S) % H, b = idx / (S * H);
-  const size_t rs = (size_t)3 * H * D;
-  const float* base = qkv + (size_t)b * S * rs;
-  const float* qr = base + (size_t)i * rs + hh * D;
-  float acc[D];
+__device__ __forceinline__ void rows_f32(const float* p, f32x4_t (&f)[D / 8]) {
 #pragma unroll
-  for (int d = 0; d < D; ++d) acc[d] = 0.0f;
-  float m = -INFINITY, l = 0.0f;
-  for (int j = 0; j <= i; ++j) {
-    const float* kr = base + (size_t)j * rs + (size_t)H * D + hh * D;
-    const float* vr = kr + (size_t)H * D;
-    float s = 0.0f;
+  for (int c = 0; c < D / 8; ++c) f[c] = *reinterpret_cast<const f32x4_t*>(p + 8 * c);
+}
+
+// x[row of a][row of b] = a . b over the D columns.
+template <int D>
+__device__ __forceinline__ void dot_f32(const f32x4_t (&a)[D / 8], const f32x4_t (&b)[D / 8], f32x16_t& x) {
 #pragma unroll
-    for (int d = 0; d < D; ++d) s += qr[d] * kr[d];
-    s *= scale;
-    const float mn = fmaxf(m, s);
-    const float a = expf(m - mn), p = expf(s - mn);
-    l = l * a + p;
+  for (int r = 0; r < 16; ++r) x[r] = 0.0f;
 #pragma unroll
-    for (int d = 0; d < D; ++d) acc[d] = acc[d] * a + p * vr[d];
-    m = mn;
-  }
-  float* orow = o + ((size_t)b * S + i) * H * D + hh * D;
+  for (int c = 0; c < D / 8; ++c)
 #pragma unroll
-  for (int d = 0; d < D; ++d) orow[d] = acc[d] / l;
-  lse[((size_t)b * H + hh) * S + i] = m + logf(l);
+    for (int j = 0; j < 4; ++j) x = __builtin_amdgcn_mfma_f32_32x32x2f32(a[c][j], b[c][j], x, 0, 0, 0);
+}
+
+// acc[column][lane's row] += sum over the tile's 32 rows of t[row][column] x[row].
+// `t`: the tile's first row plus the lane's 4 h rows and l32 columns.
+template <int D>
+__device__ __forceinline__ void accumulate_f32(const float* t, size_t ld, const f32x16_t& x, f32x16_t (&acc)[D / 32]) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r)
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt)
+      acc[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(t[(size_t)((r >> 2) * 8 + (r & 3)) * ld + dt * 32], x[r], acc[dt],
+                                                     0, 0, 0);
 }
 
 template <int D>
-__global__ void __launch_bounds__(128) attn_bwd_dq_f32(int B, int S, int H, const float* __restrict__ qkv,
-                                                       const float* __restrict__ dout, const float* __restrict__ lse,
-                                                       const float* __restrict__ delta, float* __restrict__ dqkv,
-                                                       float scale) {
-  const int idx = blockIdx.x * 128 + threadIdx.x;
-  if (idx >= B * H * S) return;
-  const int i = idx % S, hh = (idx / S) % H, b = idx / (S * H);
-  const size_t rs = (size_t)3 * H * D;
-  const float* base = qkv + (size_t)b * S * rs;
-  const float* qr = base + (size_t)i * rs + hh * D;
-  const float* dor = dout + ((size_t)b * S + i) * H * D + hh * D;
-  const float L = lse[((size_t)b * H + hh) * S + i];
-  const float del = delta[((size_t)b * H + hh) * S + i];
-  float acc[D];
+constexpr size_t f32_lds_bytes() { return (size_t)4 * D * 32 * 4 + 4 * 64 * 4; }
+
+// Sum of the four waves' accumulators, times f, to rows of stride ld (`out`:
+// the lane's row, first column).
+template <int D>
+__device__ __forceinline__ void merge_f32(char* smem, const f32x16_t (&acc)[D / 32], float f, float* out, int wave,
+                                          int lane) {
+  float* part = reinterpret_cast<float*>(smem);
+  __syncthreads();
 #pragma unroll
-  for (int d = 0; d < D; ++d) acc[d] = 0.0f;
-  for (int j = 0; j <= i; ++j) {
-    const float* kr = base + (size_t)j * rs + (size_t)H * D + hh * D;
-    const float* vr = kr + (size_t)H * D;
-    float s = 0.0f, dp = 0.0f;
+  for (int dt = 0; dt < D / 32; ++dt)
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-      s += qr[d] * kr[d];
-      dp += dor[d] * vr[d];
+    for (int r = 0; r < 16; ++r) part[((wave * (D / 32) + dt) * 16 + r) * 64 + lane] = acc[dt][r];
+  __syncthreads();
+#pragma unroll
+  for (int dt = 0; dt < D / 32; ++dt) {  // wave w: registers 4 w .. 4 w + 3 of every column group
+    float v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[e] = 0.0f;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) v[e] += part[((w * (D / 32) + dt) * 16 + wave * 4 + e) * 64 + lane];
+      v[e] *= f;
     }
-    const float p = expf(s * scale - L);
-    const float ds = p * (dp - del);
-#pragma unroll
-    for (int d = 0; d < D; ++d) acc[d] += ds * kr[d];
+    store4(out + dt * 32 + wave * 8 + (lane >> 5) * 4, v);
   }
-  float* out = dqkv + ((size_t)b * S + i) * rs + hh * D;
-#pragma unroll
-  for (int d = 0; d < D; ++d) out[d] = acc[d] * scale;
 }
 
 template <int D>
-__global__ void __launch_bounds__(128) attn_bwd_dkdv_f32(int B, int S, int H, const float* __restrict__ qkv,
+__global__ void __launch_bounds__(256) attn_fwd_f32(int S, int H, int Bm, int mstride, const float* __restrict__ qkv,
+                                                    float* __restrict__ o, float* __restrict__ lse, float scale) {
+  extern __shared__ __align__(16) char smem[];
+  const int b = seq_index(blockIdx.x / H, Bm, mstride), hh = blockIdx.x % H;
+  const int qt = gridDim.y - 1 - blockIdx.y;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hf = lane >> 5;
+  const int q = qt * 32 + l32;
+  const size_t rs = (size_t)3 * H * D;
+  const float* base = qkv + (size_t)b * S * rs + (size_t)hh * D;
+  const float* Kp = base + (size_t)H * D;
+  const float* Vp = Kp + (size_t)H * D;
+  f32x4_t qf[D / 8];
+  rows_f32<D>(base + (size_t)q * rs + 4 * hf, qf);
+  f32x16_t oacc[D / 32];
+#pragma unroll
+  for (int t = 0; t < D / 32; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) oacc[t][r] = 0.0f;
+  float m = -INFINITY, l = 0.0f;
+  for (int t = wave; t <= qt; t += 4) {
+    f32x4_t kf[D / 8];
+    f32x16_t s;
+    rows_f32<D>(Kp + (size_t)(t * 32 + l32) * rs + 4 * hf, kf);
+    dot_f32<D>(kf, qf, s);  // s[r]: key 32 t + (r/4)*8 + 4*hf + r%4, query q
+    float mloc = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      s[r] = t * 32 + (r >> 2) * 8 + hf * 4 + (r & 3) > q ? -INFINITY : s[r] * scale;
+      mloc = fmaxf(mloc, s[r]);
+    }
+    const float mn = fmaxf(m, half_max(mloc));
+    const float alpha = expf(m - mn);  // every tile has an unmasked key for each query
+    l *= alpha;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      s[r] = expf(s[r] - mn);
+      l += s[r];
+    }
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) oacc[dt][r] *= alpha;
+    m = mn;
+    accumulate_f32<D>(Vp + (size_t)(t * 32 + hf * 4) * rs + l32, rs, s, oacc);
+  }
+  // Online-softmax merge: common maximum and sum of each row, then plain sums.
+  float* ml = reinterpret_cast<float*>(smem + (size_t)4 * D * 32 * 4);
+  l = half_sum(l);
+  if (hf == 0) {
+    ml[wave * 64 + l32] = m;
+    ml[wave * 64 + 32 + l32] = l;
+  }
+  __syncthreads();
+  float mt = -INFINITY, lt = 0.0f;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) mt = fmaxf(mt, ml[w * 64 + l32]);
+#pragma unroll
+  for (int w = 0; w < 4; ++w) lt += ml[w * 64 + 32 + l32] * expf(ml[w * 64 + l32] - mt);
+  const float a = expf(m - mt) / lt;
+#pragma unroll
+  for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) oacc[dt][r] *= a;
+  merge_f32<D>(smem, oacc, 1.0f, o + (((size_t)b * S + q) * H + hh) * D, wave, lane);
+  if (wave == 0 && hf == 0) lse[((size_t)b * H + hh) * S + q] = mt + logf(lt);
+}
+
+// dQ, and delta = dO . O of its rows for the dK/dV kernel launched after it.
+template <int D>
+__global__ void __launch_bounds__(256) attn_bwd_dq_f32(int S, int H, int Bm, int mstride,
+                                                       const float* __restrict__ qkv, const float* __restrict__ o,
+                                                       const float* __restrict__ dout, const float* __restrict__ lse,
+                                                       float* __restrict__ delta, float* __restrict__ dqkv,
+                                                       float scale) {
+  extern __shared__ __align__(16) char smem[];
+  const int b = seq_index(blockIdx.x / H, Bm, mstride), hh = blockIdx.x % H;
+  const int qt = gridDim.y - 1 - blockIdx.y;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hf = lane >> 5;
+  const int q = qt * 32 + l32;
+  const size_t rs = (size_t)3 * H * D, row = (((size_t)b * S + q) * H + hh) * D;
+  const float* base = qkv + (size_t)b * S * rs + (size_t)hh * D;
+  const float* Kp = base + (size_t)H * D;
+  const float* Vp = Kp + (size_t)H * D;
+  f32x4_t qf[D / 8], of[D / 8];
+  rows_f32<D>(base + (size_t)q * rs + 4 * hf, qf);
+  rows_f32<D>(dout + row + 4 * hf, of);
+  const float L = lse[((size_t)b * H + hh) * S + q];
+  float part = 0.0f;
+#pragma unroll
+  for (int c = 0; c < D / 8; ++c) {
+    const f32x4_t ov = *reinterpret_cast<const f32x4_t*>(o + row + 4 * hf + 8 * c);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) part += of[c][e] * ov[e];
+  }
+  const float del = half_sum(part);
+  if (wave == 0 && hf == 0) delta[((size_t)b * H + hh) * S + q] = del;
+  f32x16_t dq[D / 32];
+#pragma unroll
+  for (int t = 0; t < D / 32; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) dq[t][r] = 0.0f;
+  for (int t = wave; t <= qt; t += 4) {
+    f32x4_t f[D / 8];
+    f32x16_t p, dp;
+    rows_f32<D>(Kp + (size_t)(t * 32 + l32) * rs + 4 * hf, f);
+    dot_f32<D>(f, qf, p);
+    rows_f32<D>(Vp + (size_t)(t * 32 + l32) * rs + 4 * hf, f);
+    dot_f32<D>(f, of, dp);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const bool masked = t * 32 + (r >> 2) * 8 + hf * 4 + (r & 3) > q;
+      p[r] = masked ? 0.0f : expf(p[r] * scale - L) * (dp[r] - del);
+    }
+    accumulate_f32<D>(Kp + (size_t)(t * 32 + hf * 4) * rs + l32, rs, p, dq);
+  }
+  merge_f32<D>(smem, dq, scale, dqkv + ((size_t)b * S + q) * rs + (size_t)hh * D, wave, lane);
+}
+
+template <int D>
+__global__ void __launch_bounds__(256) attn_bwd_dkdv_f32(int S, int H, int Bm, int mstride,
+                                                         const float* __restrict__ qkv,
                                                          const float* __restrict__ dout,
                                                          const float* __restrict__ lse,
-                                                         const float* __restrict__ delta,
-                                                         float* __restrict__ dqkv, float scale) {
-  const int idx = blockIdx.x * 128 + threadIdx.x;
-  if (idx >= B * H * S) return;
-  const int j = idx % S, hh = (idx / S) % H, b = idx / (S * H);
-  const size_t rs = (size_t)3 * H * D;
-  const float* base = qkv + (size_t)b * S * rs;
-  const float* kr = base + (size_t)j * rs + (size_t)H * D + hh * D;
-  const float* vr = kr + (size_t)H * D;
-  float dk[D], dv[D];
+                                                         const float* __restrict__ delta, float* __restrict__ dqkv,
+                                                         float scale) {
+  extern __shared__ __align__(16) char smem[];
+  const int b = seq_index(blockIdx.x / H, Bm, mstride), hh = blockIdx.x % H;
+  const int kt = blockIdx.y;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hf = lane >> 5;
+  const int key = kt * 32 + l32;
+  const size_t rs = (size_t)3 * H * D, ors = (size_t)H * D;
+  const float* base = qkv + (size_t)b * S * rs + (size_t)hh * D;
+  const float* dop = dout + (size_t)b * S * ors + (size_t)hh * D;
+  const float* lp = lse + ((size_t)b * H + hh) * S;
+  const float* dlp = delta + ((size_t)b * H + hh) * S;
+  f32x4_t kf[D / 8], vf[D / 8];
+  rows_f32<D>(base + (size_t)key * rs + (size_t)H * D + 4 * hf, kf);
+  rows_f32<D>(base + (size_t)key * rs + (size_t)2 * H * D + 4 * hf, vf);
+  f32x16_t dk[D / 32], dv[D / 32];
 #pragma unroll
-  for (int d = 0; d < D; ++d) dk[d] = dv[d] = 0.0f;
-  for (int i = j; i < S; ++i) {
-    const float* qr = base + (size_t)i * rs + hh * D;
-    const float* dor = dout + ((size_t)b * S + i) * H * D + hh * D;
-    float s = 0.0f, dp = 0.0f;
+  for (int t = 0; t < D / 32; ++t)
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-      s += qr[d] * kr[d];
-      dp += dor[d] * vr[d];
+    for (int r = 0; r < 16; ++r) dk[t][r] = dv[t][r] = 0.0f;
+  for (int t = kt + wave; t < S / 32; t += 4) {
+    f32x4_t f[D / 8];
+    f32x16_t p, dp;
+    rows_f32<D>(base + (size_t)(t * 32 + l32) * rs + 4 * hf, f);
+    dot_f32<D>(f, kf, p);  // p[r]: query 32 t + (r/4)*8 + 4*hf + r%4, key `key`
+    rows_f32<D>(dop + (size_t)(t * 32 + l32) * ors + 4 * hf, f);
+    dot_f32<D>(f, vf, dp);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int q = t * 32 + (r >> 2) * 8 + hf * 4 + (r & 3);
+      p[r] = q < key ? 0.0f : expf(p[r] * scale - lp[q]);
+      dp[r] = p[r] * (dp[r] - dlp[q]);
     }
-    const float p = expf(s * scale - lse[((size_t)b * H + hh) * S + i]);
-    const float ds = p * (dp - delta[((size_t)b * H + hh) * S + i]);
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-      dv[d] += p * dor[d];
-      dk[d] += ds * qr[d];
-    }
+    accumulate_f32<D>(dop + (size_t)(t * 32 + hf * 4) * ors + l32, ors, p, dv);
+    accumulate_f32<D>(base + (size_t)(t * 32 + hf * 4) * rs + l32, rs, dp, dk);
   }
-  float* ko = dqkv + ((size_t)b * S + j) * rs + (size_t)H * D + hh * D;
-  float* vo = ko + (size_t)H * D;
-#pragma unroll
-  for (int d = 0; d < D; ++d) {
-    ko[d] = dk[d] * scale;
-    vo[d] = dv[d];
-  }
+  float* ko = dqkv + ((size_t)b * S + key) * rs + (size_t)H * D + (size_t)hh * D;
+  merge_f32<D>(smem, dk, scale, ko, wave, lane);
+  merge_f32<D>(smem, dv, 1.0f, ko + (size_t)H * D, wave, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -985,13 +1079,12 @@ static hipError_t fwd_d(int dtype, int B, int S, int H, int G, int mstride, cons
     hipLaunchKernelGGL((attn_fwd_bf16<D>), dim3((unsigned)n_pairs * (S / 64)), dim3(256), lds, st, S, H, B, mstride,
                        (const bf16_t*)qkv, (bf16_t*)o, lse, scale * kLog2e, n_pairs, attn_order(n_pairs, S, D));
   } else {
-    const size_t rs = (size_t)3 * H * D, seq_rows = (size_t)mstride * S;
-    for (int m = 0; m < G; ++m) {
-      dim3 grid((B * H * S + 127) / 128);
-      hipLaunchKernelGGL((attn_fwd_f32<D>), grid, dim3(128), 0, st, B, S, H,
-                         (const float*)qkv + m * seq_rows * rs, (float*)o + m * seq_rows * H * D,
-                         lse + m * seq_rows * H, scale);
-    }
+    constexpr size_t lds = f32_lds_bytes<D>();
+    static std::atomic<uint64_t> ok{0};
+    hipError_t e = allow_lds(attn_fwd_f32<D>, lds, ok);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((attn_fwd_f32<D>), dim3((unsigned)(H * G * B), S / 32), dim3(256), lds, st, S, H, B, mstride,
+                       (const float*)qkv, (float*)o, lse, scale);
   }
   return hipGetLastError();
 }
@@ -1000,7 +1093,6 @@ template <int D>
 static hipError_t bwd_d(int dtype, int B, int S, int H, int G, int mstride, const void* qkv, const void* o,
                         const float* lse, const void* dout, void* dqkv, float* delta, hipStream_t st) {
   const float scale = 1.0f / sqrtf((float)D);
-  const int rows = G * B * S * H;
   if (dtype == DT_BF16) {
     constexpr size_t lds_q = fwd_lds_bytes<D>(), lds_k = bwd_lds_bytes<D>();
     static_assert(lds_k <= 160 * 1024, "LDS budget");
@@ -1018,21 +1110,16 @@ static hipError_t bwd_d(int dtype, int B, int S, int H, int G, int mstride, cons
     hipLaunchKernelGGL((attn_bwd_dkdv_bf16<D>), grid, dim3(256), lds_k, st, S, H, B, mstride, (const bf16_t*)qkv,
                        (const bf16_t*)dout, lse, delta, (bf16_t*)dqkv, scale * kLog2e, scale, n_pairs, ord);
   } else {
-    hipLaunchKernelGGL((attn_delta_kernel<float, D>), dim3((rows + 255) / 256), dim3(256), 0, st, G * B, S, H, B,
-                       mstride, (const float*)o, (const float*)dout, delta);
-    const size_t rs = (size_t)3 * H * D, seq_rows = (size_t)mstride * S;
-    for (int m = 0; m < G; ++m) {
-      const float* q_m = (const float*)qkv + m * seq_rows * rs;
-      const float* do_m = (const float*)dout + m * seq_rows * H * D;
-      const float* lse_m = lse + m * seq_rows * H;
-      const float* del_m = delta + m * seq_rows * H;
-      float* dq_m = (float*)dqkv + m * seq_rows * rs;
-      dim3 grid((B * H * S + 127) / 128);
-      hipLaunchKernelGGL((attn_bwd_dkdv_f32<D>), grid, dim3(128), 0, st, B, S, H, q_m, do_m, lse_m, del_m, dq_m,
-                         scale);
-      hipLaunchKernelGGL((attn_bwd_dq_f32<D>), grid, dim3(128), 0, st, B, S, H, q_m, do_m, lse_m, del_m, dq_m,
-                         scale);
-    }
+    constexpr size_t lds = f32_lds_bytes<D>();
+    static std::atomic<uint64_t> ok_k{0}, ok_q{0};
+    hipError_t e = allow_lds(attn_bwd_dkdv_f32<D>, lds, ok_k);
+    if (e == hipSuccess) e = allow_lds(attn_bwd_dq_f32<D>, lds, ok_q);
+    if (e != hipSuccess) return e;
+    const dim3 grid((unsigned)(H * G * B), S / 32);
+    hipLaunchKernelGGL((attn_bwd_dq_f32<D>), grid, dim3(256), lds, st, S, H, B, mstride, (const float*)qkv,
+                       (const float*)o, (const float*)dout, lse, delta, (float*)dqkv, scale);
+    hipLaunchKernelGGL((attn_bwd_dkdv_f32<D>), grid, dim3(256), lds, st, S, H, B, mstride, (const float*)qkv,
+                       (const float*)dout, lse, delta, (float*)dqkv, scale);
   }
   return hipGetLastError();
 }

@@ -18,8 +18,8 @@
 // vector.  Workgroups are mapped to tiles so that each of the 8 XCDs works on
 // a compact block of neighbouring tiles (operand reuse in its own L2).
 //
-// fp32 check mode: a plain LDS-tiled FMA kernel with the same layouts and
-// epilogues.
+// fp32 check mode: fp32 matrix instructions on 32 x 32 tiles, the same layouts
+// and epilogues.
 #include <atomic>
 #include <type_traits>
 
@@ -541,55 +541,79 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_mfma_kernel(GemmBatch batch
 }
 
 // ---------------------------------------------------------------------------
-// fp32 check-mode kernel: 64x64 tile, BK = 16, 4x4 outputs per thread.
+// fp32 check-mode kernel, on the fp32 matrix instruction (32x32x2: fp32 products
+// and sums).  A workgroup owns a 32 x 32 tile; its four waves split K and their
+// sums are added in wave order.  Operands go straight from global memory to
+// registers, fetched one 16-deep group ahead: the product's k index h (= lane /
+// 32) of step j of chunk c is taken to mean k = 8 c + 4 h + j, so a lane reads
+// 16 bytes of a K-contiguous row (or four k-rows of an M- or N-contiguous
+// operand, 32 lanes side by side).  Small problems are bound by latency: a
+// 64 x 64 FMA tile, loaded and then used, took 20 us at 256 x 256 x 256 and 68 us
+// at 256 x 256 x 1024 (16 workgroups).
 // ---------------------------------------------------------------------------
+template <bool TRANS>
+__device__ __forceinline__ void frag_f32(const float* p, int ld, f32x4_t (&f)[2]) {
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    if constexpr (!TRANS) {
+      f[c] = *reinterpret_cast<const f32x4_t*>(p + 8 * c);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) f[c][j] = p[(size_t)(8 * c + j) * ld];
+    }
+  }
+}
+
 template <bool A_T, bool B_T, int EPI>
 __global__ void __launch_bounds__(256) gemm_f32_kernel(GemmBatch batch) {
-  __shared__ float As[16][64 + 4];
-  __shared__ float Bs[16][64 + 4];
+  __shared__ float red[4][32][32 + 4];
   const int bid = blockIdx.x;
   int tile0;
   const GemmProblem p = select_problem(batch, bid, &tile0);
   const int tile = bid - tile0;
-  const int tiles_n = (p.N + 63) / 64;
-  const int m0 = (tile / tiles_n) * 64;
-  const int n0 = (tile % tiles_n) * 64;
-  const float* A = reinterpret_cast<const float*>(p.a);
-  const float* B = reinterpret_cast<const float*>(p.b);
-  const int tid = threadIdx.x;
-  const int ty = tid >> 4, tx = tid & 15;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < p.K; k0 += 16) {
+  const int tiles_n = p.N / 32;
+  const int m0 = (tile / tiles_n) * 32, n0 = (tile % tiles_n) * 32;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, hf = lane >> 5;
+  const int kw = p.K / 4;  // a multiple of 16
+  const size_t k0 = (size_t)wave * kw + 4 * hf;
+  const float* a = reinterpret_cast<const float*>(p.a) + (A_T ? k0 * p.lda + m0 + l32 : (size_t)(m0 + l32) * p.lda + k0);
+  const float* b = reinterpret_cast<const float*>(p.b) + (B_T ? k0 * p.ldb + n0 + l32 : (size_t)(n0 + l32) * p.ldb + k0);
+  const size_t sa = A_T ? (size_t)16 * p.lda : 16, sb = B_T ? (size_t)16 * p.ldb : 16;
+  f32x16_t acc;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      int idx = tid + e * 256;
-      int m, k, n, kb;
-      if (!A_T) { m = idx >> 4; k = idx & 15; } else { k = idx >> 6; m = idx & 63; }
-      int gm = min(m0 + m, p.M - 1);
-      As[k][m] = A_T ? A[(size_t)(k0 + k) * p.lda + gm] : A[(size_t)gm * p.lda + k0 + k];
-      if (!B_T) { n = idx >> 4; kb = idx & 15; } else { kb = idx >> 6; n = idx & 63; }
-      int gn = min(n0 + n, p.N - 1);
-      Bs[kb][n] = B_T ? B[(size_t)(k0 + kb) * p.ldb + gn] : B[(size_t)gn * p.ldb + k0 + kb];
+  for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+  f32x4_t fa[2], fb[2];
+  frag_f32<A_T>(a, p.lda, fa);
+  frag_f32<B_T>(b, p.ldb, fb);
+  for (int k = 16; k <= kw; k += 16) {
+    f32x4_t na[2], nb[2];
+    if (k < kw) {
+      a += sa;
+      b += sb;
     }
-    __syncthreads();
+    frag_f32<A_T>(a, p.lda, na);  // the last group again after the last step (unused)
+    frag_f32<B_T>(b, p.ldb, nb);
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      float a[4], b[4];
+    for (int c = 0; c < 2; ++c)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) { a[r] = As[k][ty * 4 + r]; b[r] = Bs[k][tx * 4 + r]; }
+      for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[c][j], fb[c][j], acc, 0, 0, 0);
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[r][c] = fmaf(a[r], b[c], acc[r][c]);
+    for (int c = 0; c < 2; ++c) {
+      fa[c] = na[c];
+      fb[c] = nb[c];
     }
-    __syncthreads();
   }
+  // acc[r]: row (r/4)*8 + 4*hf + r%4, column l32.
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int m = m0 + ty * 4 + r;
-    const int n = n0 + tx * 4;
-    if (m < p.M && n < p.N) epilogue4<float, EPI>(p, m, n, acc[r]);
-  }
+  for (int r = 0; r < 16; ++r) red[wave][(r >> 2) * 8 + hf * 4 + (r & 3)][l32] = acc[r];
+  __syncthreads();
+  const int row = tid >> 3, col = (tid & 7) * 4;
+  float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int w = 0; w < 4; ++w)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] += red[w][row][col + e];
+  epilogue4<float, EPI>(p, m0 + row, n0 + col, v);
 }
 
 // ---------------------------------------------------------------------------
@@ -619,7 +643,7 @@ static hipError_t run_f32(GemmBatch& batch, hipStream_t stream) {
   int tiles = 0;
   for (int i = 0; i < batch.n_probs; ++i) {
     batch.tile_start[i] = tiles;
-    tiles += ((batch.p[i].M + 63) / 64) * ((batch.p[i].N + 63) / 64);
+    tiles += (batch.p[i].M / 32) * (batch.p[i].N / 32);
   }
   for (int i = batch.n_probs; i <= kMaxGroup; ++i) batch.tile_start[i] = tiles;
   if (tiles == 0) return hipSuccess;

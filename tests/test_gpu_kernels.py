@@ -77,6 +77,23 @@ def test_gemm_smallest_problem_on_every_tile(cfg, a_t, b_t):
     assert rel_err(c32.cpu().numpy(), ref) < 2e-5
 
 
+@pytest.mark.parametrize("a_t,b_t", [(0, 0), (0, 1), (1, 1), (1, 0)])
+@pytest.mark.parametrize("mnk", [(64, 64, 64), (128, 192, 192), (64, 320, 1024)])
+def test_gemm_fp32_k_split(mnk, a_t, b_t):
+    """fp32 kernel: K split over four waves in groups of 16 (one group each at K
+    = 64).  Tolerance: fp32 sums of up to 1024 products, as in the layout test."""
+    torch = need_gpu()
+    M, N, K = mnk
+    print(f"[gemm fp32] a_t={a_t} b_t={b_t} {mnk}", flush=True)
+    a_p, a = _rand((K, M) if a_t else (M, K), "fp32", 27)
+    b_p, b = _rand((K, N) if b_t else (N, K), "fp32", 28)
+    ref = (a.T if a_t else a) @ (b if b_t else b.T)
+    c = torch.empty((M, N), dtype=torch.float32, device="cuda")
+    B.gemm(_dev(a_p), _dev(b_p), c, M, N, K, a_trans=a_t, b_trans=b_t, epilogue=B.EPI_STORE)
+    torch.cuda.synchronize()
+    assert rel_err(B.to_host_f64(c), ref) < 1e-5
+
+
 # (M, N, K) for which the choice for a lone launch is 64x128 (or 128x128 where A
 # is read transposed), 128x128, 192x128, 128x192 and 256x128 tiles, each with
 # ragged last tiles and more K stages than the ring holds; and one K stage.
@@ -201,6 +218,7 @@ def test_column_sum(dtype, rows, cols):
 ATTN_CASES = [(dt, d, s, 2, 3) for dt in ("bf16", "fp32") for d in (64, 96, 128) for s in (128, 320)]
 ATTN_CASES += [("bf16", 128, 2048, 1, 2), ("bf16", 96, 1024, 2, 2)]  # full-length rows of the workloads
 ATTN_CASES += [("bf16", d, 64, 2, 3) for d in (64, 96, 128)]  # one block: the pair's second half is empty
+ATTN_CASES += [("fp32", d, 64, 2, 3) for d in (64, 96, 128)]  # two tiles: two of the four waves have none
 
 
 @pytest.mark.parametrize("dtype,d,seq,batch,heads", ATTN_CASES)
