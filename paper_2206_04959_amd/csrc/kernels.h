@@ -65,10 +65,11 @@ hipError_t launch_layernorm_bwd(int dtype, int rows, int h, const void* dout, co
                                 const void* dres, void* dx, hipStream_t stream, int members = 1,
                                 int member_stride = 0);
 
-// Partials [reduce_groups(rows), h] of sum(dout * xhat) and sum(dout).
-hipError_t launch_layernorm_param_partials(int dtype, int rows, int h, const void* dout, const void* x,
-                                           const float* mean, const float* rstd, float* part_g, float* part_b,
-                                           hipStream_t stream);
+// The same with the parameter gradients: dgamma (=|+=) sum(dout * xhat), dbeta
+// (=|+=) sum(dout).  part: 2 * reduce_groups(rows) * h floats.
+hipError_t launch_layernorm_bwd_full(int dtype, int rows, int h, const void* dout, const void* x, const float* mean,
+                                     const float* rstd, const void* gamma, const void* dres, void* dx, float* dgamma,
+                                     float* dbeta, int accumulate, float* part, hipStream_t stream);
 
 // Column partial sums of x [rows, cols] into part [groups, cols] fp32.
 hipError_t launch_column_partials(int dtype, int rows, int cols, const void* x, float* part,

@@ -1167,12 +1167,8 @@ int merak_layernorm_bwd(int dtype, int rows, int h, const void* dout, const void
   TRY(check_ptr(dout)); TRY(check_ptr(x)); TRY(check_ptr(mean)); TRY(check_ptr(rstd)); TRY(check_ptr(gamma));
   TRY(check_ptr(dres)); TRY(check_ptr(dx)); TRY(check_ptr(dgamma)); TRY(check_ptr(dbeta)); TRY(check_ptr(scratch));
   hipStream_t st = (hipStream_t)stream;
-  const size_t n = merak_reduce_scratch_elems(rows, h);
-  const int G = (int)reduce_groups(rows);
-  HIP_TRY(launch_layernorm_bwd(dtype, rows, h, dout, x, mean, rstd, gamma, dres, dx, st));
-  HIP_TRY(launch_layernorm_param_partials(dtype, rows, h, dout, x, mean, rstd, scratch, scratch + n, st));
-  HIP_TRY(launch_reduce_partials(G, h, scratch, dgamma, accumulate, st));
-  HIP_TRY(launch_reduce_partials(G, h, scratch + n, dbeta, accumulate, st));
+  HIP_TRY(launch_layernorm_bwd_full(dtype, rows, h, dout, x, mean, rstd, gamma, dres, dx, dgamma, dbeta, accumulate,
+                                    scratch, st));
   return MERAK_OK;
 }
 
@@ -1189,13 +1185,10 @@ int merak_layernorm_bwd_noalloc(int dtype, int rows, int h, const void* dout, co
   float* scratch = nullptr;  // the library's array on the current device
   HIP_TRY(noalloc_scratch(&scratch));
   hipStream_t st = (hipStream_t)stream;
-  const int G = (int)reduce_groups(rows);
-  // Same kernels and order as merak_layernorm_bwd; the partial-sum kernel
-  // writes every scratch element the reduction then reads.
-  HIP_TRY(launch_layernorm_bwd(dtype, rows, h, dout, x, mean, rstd, gamma, dres, dx, st));
-  HIP_TRY(launch_layernorm_param_partials(dtype, rows, h, dout, x, mean, rstd, scratch, scratch + n, st));
-  HIP_TRY(launch_reduce_partials(G, h, scratch, dgamma, accumulate, st));
-  HIP_TRY(launch_reduce_partials(G, h, scratch + n, dbeta, accumulate, st));
+  // Same kernels and order as merak_layernorm_bwd; the partial sums fill every
+  // scratch element the reduction then reads.
+  HIP_TRY(launch_layernorm_bwd_full(dtype, rows, h, dout, x, mean, rstd, gamma, dres, dx, dgamma, dbeta, accumulate,
+                                    scratch, st));
   return MERAK_OK;
 }
 

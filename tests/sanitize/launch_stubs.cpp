@@ -11,8 +11,10 @@ hipError_t launch_layernorm_fwd(int, int, int, float, const void*, const void*, 
                                 hipStream_t, int, int) { return unreachable(); }
 hipError_t launch_layernorm_bwd(int, int, int, const void*, const void*, const float*, const float*, const void*,
                                 const void*, void*, hipStream_t, int, int) { return unreachable(); }
-hipError_t launch_layernorm_param_partials(int, int, int, const void*, const void*, const float*, const float*,
-                                           float*, float*, hipStream_t) { return unreachable(); }
+hipError_t launch_layernorm_bwd_full(int, int, int, const void*, const void*, const float*, const float*, const void*,
+                                     const void*, void*, float*, float*, int, float*, hipStream_t) {
+  return unreachable();
+}
 hipError_t launch_column_partials(int, int, int, const void*, float*, hipStream_t) { return unreachable(); }
 hipError_t launch_reduce_partials(int, int, const float*, float*, int, hipStream_t) { return unreachable(); }
 hipError_t launch_column_partials_batch(int, const ColPartialJob*, int, hipStream_t) { return unreachable(); }

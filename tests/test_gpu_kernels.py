@@ -199,6 +199,39 @@ def test_layernorm_fwd_bwd(dtype, h):
     assert rel_err(db.cpu().numpy(), dbr) < 1e-5
 
 
+# one row; one segment of 64 rows and one row more; nine segments (one XCD gets
+# two of them) over widths of one, two and three 512-column slices
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("rows,h", [(1, 64), (64, 512), (65, 520), (575, 1344)])
+def test_layernorm_bwd_one_launch_equals_parts(dtype, rows, h):
+    """dx and the parameter sums made in one launch: dx against the oracle, the
+    sums within fp32 rounding of the exact sums, and accumulate adds exactly the
+    overwritten values."""
+    torch = need_gpu()
+    print(f"[layernorm bwd] {dtype} {rows}x{h}", flush=True)
+    x_p, x = _rand((rows, h), dtype, 41, std=2.0, mean=0.5)
+    g_p, g = _rand((h,), dtype, 42, std=0.1, mean=1.0)
+    do_p, do = _rand((rows, h), dtype, 43)
+    dr_p, dr = _rand((rows, h), dtype, 44)
+    _, xhat, rs = oracle.layer_norm_forward(x, g, np.zeros(h), 1e-5)
+    dz, dgr, dbr = oracle.layer_norm_backward(do, xhat, rs, g)
+    mean = torch.from_numpy(x.mean(1).astype(np.float32)).cuda()
+    rstd = torch.from_numpy(rs[:, 0].astype(np.float32)).cuda()
+    dx = torch.empty((rows, h), dtype=torch.bfloat16 if dtype == "bf16" else torch.float32, device="cuda")
+    dg = torch.full((h,), float("nan"), dtype=torch.float32, device="cuda")
+    db = torch.full((h,), float("nan"), dtype=torch.float32, device="cuda")
+    scratch = torch.full((2 * B.reduce_scratch_elems(rows, h),), float("nan"), dtype=torch.float32, device="cuda")
+    args = (_dev(do_p), _dev(x_p), mean, rstd, _dev(g_p), _dev(dr_p), dx, dg, db, scratch)
+    B.layernorm_bwd(*args)
+    torch.cuda.synchronize()
+    assert rel_err(B.to_host_f64(dx), dr + dz) < (1e-2 if dtype == "bf16" else 1e-5)
+    assert rel_err(dg.cpu().numpy(), dgr) < 1e-4 and rel_err(db.cpu().numpy(), dbr) < 1e-5
+    dg1, db1 = dg.clone(), db.clone()
+    B.layernorm_bwd(*args, accumulate=True)
+    torch.cuda.synchronize()
+    assert torch.equal(dg, dg1 + dg1) and torch.equal(db, db1 + db1)
+
+
 # one row of one 8-column chunk, a ragged column count over a partial
 # reduction segment, and a width past one workgroup's 512 columns
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
