@@ -181,7 +181,7 @@ int merak_stage_recompute(merak_stage_t stage, const void* params, void* stream0
  *                 AllReduces.
  * Weight gradients are computed per block over the whole micro-batch once all
  * its sub-micro-batches are done (deterministic; no floating-point atomics), on
- * a stream of the library that one handle's backward calls share with another's.
+ * a stream of the library that handles used on one caller stream share.
  * MERAK_ERR_ORDER if no forward pass is pending, if the mask is nonzero and
  * merak_stage_recompute has not run since the forward pass, or if another
  * handle has recomputed into a shared recompute area since.  Consumes the

@@ -245,19 +245,28 @@ std::mutex g_mu;
 std::map<void*, merak_stage*> g_rc_owner;  // recompute area -> handle that last filled it
 
 // The streams for weight gradients.  Every handle has one; a backward call uses
-// that of the device's oldest handle, so that calls made one after the other,
-// on any handles, keep the weight gradients on one stream.  With each handle on
-// its own, the streams of a program with several handles exceed HIP's default
-// of four hardware queues, the library's stream then shares a queue with one of
-// the caller's, and the weight gradients run in turn with the chains instead of
+// the stream of the device's oldest handle that last served the same caller
+// stream, so that calls made one after the other on one pair of streams, with
+// any handles, keep the weight gradients on one stream.  With each handle on its
+// own, the streams of a program with several handles exceed HIP's default of
+// four hardware queues, the library's stream then shares a queue with one of the
+// caller's, and the weight gradients run in turn with the chains instead of
 // beside them: with three handles the 8.3B-shaped step took 11.0 ms against
 // 10.0 with one, the 1.5B-shaped 13.3 against 11.9, the 2.5B-shaped 6.9 against
-// 5.7 and the 20B-shaped 15.8 against 14.9.  A call uses its own handle's stream
-// where the oldest one's is in use by another host thread's call, and always
-// under graph capture.
+// 5.7 and the 20B-shaped 15.8 against 14.9.
+//
+// Only calls on one caller stream share: those wait for each other on it in any
+// case (a backward call ends with the caller's stream waiting for the weight
+// gradients, and the next one's start with what the caller's stream has reached),
+// so handles on streams of their own, where one may be held back by a receive
+// that another's work has to answer, never wait for each other.  Under graph
+// capture, and while another host thread's call has the shared stream, a call
+// uses its own handle's.
 struct AuxStream {
   hipStream_t st = nullptr;
-  bool busy = false;  // lent to a call that is enqueueing; under g_mu
+  bool busy = false;          // lent to a call that is enqueueing; under g_mu
+  bool served = false;        // an eager call has used it, on caller stream `caller`
+  hipStream_t caller = nullptr;
   ~AuxStream() {
     if (st) (void)hipStreamDestroy(st);
   }
@@ -273,19 +282,31 @@ bool capturing(hipStream_t st) {
   return true;
 }
 
+void drop_aux(int dev, const AuxRef& a) {
+  std::lock_guard<std::mutex> lk(g_mu);
+  std::vector<AuxRef>& all = g_aux[dev];
+  all.erase(std::find(all.begin(), all.end(), a));
+}
+
 // The stream lent to one backward call, for as long as it enqueues.
 class AuxLoan {
  public:
   AuxLoan(int dev, const AuxRef& own, hipStream_t s0) {
     const bool capture = capturing(s0);
     std::unique_lock<std::mutex> lk(g_mu);
-    const std::vector<AuxRef>& all = g_aux[dev];
-    if (!capture && !all.empty() && !all.front()->busy && !capturing(all.front()->st)) {
-      ref_ = all.front();
-    } else {
+    if (!capture) {
+      for (const AuxRef& a : g_aux[dev])
+        if (a->served && a->caller == s0 && !a->busy) {
+          ref_ = a;
+          break;
+        }
+    }
+    if (!ref_) {
       g_aux_free.wait(lk, [&] { return !own->busy; });  // at most for another call's enqueueing
       ref_ = own;
     }
+    ref_->served = !capture;  // a stream that a capture has taken is not lent
+    ref_->caller = s0;
     ref_->busy = true;
   }
   ~AuxLoan() {
@@ -684,15 +705,19 @@ int merak_stage_create(const merak_stage_config* cfg, void* workspace, size_t wo
   S->t_count = 0;
   S->t_overflow = false;
   hipError_t e = hipGetDevice(&S->dev);
+  if (e != hipSuccess) {
+    delete S;
+    return MERAK_ERR_HIP;
+  }
   try {
     S->aux = std::make_shared<AuxStream>();
     std::lock_guard<std::mutex> lk(g_mu);
-    g_aux[S->dev].reserve(g_aux[S->dev].size() + 1);  // room for this handle's entry below
+    g_aux[S->dev].push_back(S->aux);  // lent to no other handle before this one's first backward call
   } catch (const std::bad_alloc&) {
     delete S;
     return MERAK_ERR_INVALID_ARG;
   }
-  if (e == hipSuccess) e = hipStreamCreateWithFlags(&S->aux->st, hipStreamNonBlocking);
+  e = hipStreamCreateWithFlags(&S->aux->st, hipStreamNonBlocking);
   hipEvent_t* evs[] = {&S->ev_fork, &S->ev_s1, &S->ev_j0, &S->ev_j1, &S->ev_aux, &S->ev_dw[0], &S->ev_dw[1]};
   int made = 0;
   for (hipEvent_t* ev : evs) {
@@ -717,12 +742,9 @@ int merak_stage_create(const merak_stage_config* cfg, void* workspace, size_t wo
       (void)hipEventDestroy(S->ev_rc[l][0]);
       (void)hipEventDestroy(S->ev_rc[l][1]);
     }
+    drop_aux(S->dev, S->aux);
     delete S;
     return MERAK_ERR_HIP;
-  }
-  {
-    std::lock_guard<std::mutex> lk(g_mu);
-    g_aux[S->dev].push_back(S->aux);
   }
   *out = S;
   return MERAK_OK;
@@ -734,9 +756,8 @@ int merak_stage_destroy(merak_stage_t S) {
     std::lock_guard<std::mutex> lk(g_mu);
     for (auto it = g_rc_owner.begin(); it != g_rc_owner.end();)
       it = (it->second == S) ? g_rc_owner.erase(it) : std::next(it);
-    std::vector<AuxRef>& all = g_aux[S->dev];
-    all.erase(std::find(all.begin(), all.end(), S->aux));
   }
+  drop_aux(S->dev, S->aux);
   hipEvent_t evs[] = {S->ev_fork, S->ev_s1, S->ev_j0, S->ev_j1, S->ev_aux, S->ev_dw[0], S->ev_dw[1]};
   for (hipEvent_t ev : evs) (void)hipEventDestroy(ev);
   for (int l = 0; l < S->D.L; ++l) {

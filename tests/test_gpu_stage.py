@@ -241,25 +241,36 @@ SHARED = synth.StageShape("shared", n_blocks=3, hidden=256, n_heads=4, ffn=1024,
                           tp_degree=1, n_sub=2, recompute_mask=0b001, seed=77)
 
 
-def test_backward_calls_of_several_handles():
-    """Backward calls of several handles share one handle's stream: handles used
-    in turn, and a handle used after the one that owns the stream was destroyed,
-    each give the bits of a handle used alone."""
+@pytest.mark.parametrize("pairs", [(0, 0, 0), (0, 1, 2), (0, 0, 1)])
+def test_backward_calls_of_several_handles(pairs):
+    """Backward calls on one caller stream share a handle's weight-gradient
+    stream: handles used in turn on one pair of streams, on pairs of their own
+    and on both, handles that then change pairs, and a handle used after the one
+    that owns the stream was destroyed, each give the bits of a handle used
+    alone.  (pairs: which pair of streams each handle runs on.)"""
     torch = need_gpu()
+    print(f"[several handles] pairs {pairs}", flush=True)
     shapes = [SHARED.replace(seed=77 + i) for i in range(3)]
     alone = [StageRun(s).run().raw() for s in shapes]
     runs = [StageRun(s) for s in shapes]
     torch.cuda.synchronize()
     for _ in range(2):  # in turn, nothing waited for in between
-        for r in runs:
-            _step(r, r.streams)
+        for r, p in zip(runs, pairs):
+            _step(r, runs[p].streams)
+    torch.cuda.synchronize()
+    assert all(_same(r.raw(), a) for r, a in zip(runs, alone))
+    for r in runs:
+        r.grads.fill_(float("nan"))
+    torch.cuda.synchronize()
+    for r in runs:
+        _step(r, runs[2].streams)
     torch.cuda.synchronize()
     assert all(_same(r.raw(), a) for r, a in zip(runs, alone))
     for i in (1, 2):
         runs[i - 1].stage.close()
         runs[i].grads.fill_(float("nan"))
         torch.cuda.synchronize()
-        _step(runs[i], runs[i].streams)
+        _step(runs[i], runs[2].streams)
         torch.cuda.synchronize()
         assert _same(runs[i].raw(), alone[i])
 
