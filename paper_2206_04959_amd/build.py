@@ -17,7 +17,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libmerak_stage.so")
-SOURCES = ("gemm.hip", "attention.hip", "norm.hip", "stage.cpp", "graph_shard.cpp")
+SOURCES = ("gemm.hip", "attention.hip", "attention_d128.hip", "norm.hip", "stage.cpp", "graph_shard.cpp")
 
 ARCH = "gfx950"
 # Packed fp32 instructions are kept out of every code object.
@@ -36,7 +36,7 @@ def _hipcc() -> str:
 # Per-source extra flags: attention keeps its MFMA accumulators in ordinary
 # VGPRs (the online softmax rescales them between MFMAs; AGPR accumulators
 # would be copied out and back every key block).
-EXTRA_FLAGS = {"attention.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+EXTRA_FLAGS = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form"] for f in ("attention.hip", "attention_d128.hip")}
 
 
 def _compile(src: str, obj: str) -> str:

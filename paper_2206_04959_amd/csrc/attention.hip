@@ -1070,6 +1070,8 @@ template <int D>
 static hipError_t fwd_d(int dtype, int B, int S, int H, int G, int mstride, const void* qkv, void* o, float* lse,
                         hipStream_t st) {
   const float scale = 1.0f / sqrtf((float)D);
+  if constexpr (D == 128)
+    if (dtype == DT_BF16) return launch_attention_fwd_d128(B, S, H, G, mstride, qkv, o, lse, st);
   if (dtype == DT_BF16) {
     constexpr size_t lds = fwd_lds_bytes<D>();
     static std::atomic<uint64_t> ok{0};
@@ -1093,6 +1095,9 @@ template <int D>
 static hipError_t bwd_d(int dtype, int B, int S, int H, int G, int mstride, const void* qkv, const void* o,
                         const float* lse, const void* dout, void* dqkv, float* delta, hipStream_t st) {
   const float scale = 1.0f / sqrtf((float)D);
+  if constexpr (D == 128)
+    if (dtype == DT_BF16)
+      return launch_attention_bwd_d128(B, S, H, G, mstride, qkv, o, lse, dout, dqkv, delta, st);
   if (dtype == DT_BF16) {
     constexpr size_t lds_q = fwd_lds_bytes<D>(), lds_k = bwd_lds_bytes<D>();
     static_assert(lds_k <= 160 * 1024, "LDS budget");
