@@ -226,6 +226,7 @@ struct merak_stage {
   char* rc;
   int dev;  // the device current at creation
   std::shared_ptr<AuxStream> aux;
+  std::vector<std::shared_ptr<AuxStream>> borrowed;  // other handles' streams its calls have used; under g_mu
   hipEvent_t ev_fork, ev_s1, ev_j0, ev_j1, ev_aux, ev_dw[2];
   hipEvent_t ev_rc[kMaxBlocks][2];  // recompute of block l done on its two streams
   int state;  // 0 idle, 1 forward pending, 2 recomputed
@@ -261,7 +262,9 @@ std::map<void*, merak_stage*> g_rc_owner;  // recompute area -> handle that last
 // so handles on streams of their own, where one may be held back by a receive
 // that another's work has to answer, never wait for each other.  Under graph
 // capture, and while another host thread's call has the shared stream, a call
-// uses its own handle's.
+// uses its own handle's.  A handle keeps every stream that its calls have used
+// until it is destroyed, after its work: the handle a stream was made for may go
+// earlier, while another's weight gradients are still queued on it.
 struct AuxStream {
   hipStream_t st = nullptr;
   bool busy = false;          // lent to a call that is enqueueing; under g_mu
@@ -291,12 +294,13 @@ void drop_aux(int dev, const AuxRef& a) {
 // The stream lent to one backward call, for as long as it enqueues.
 class AuxLoan {
  public:
-  AuxLoan(int dev, const AuxRef& own, hipStream_t s0) {
+  AuxLoan(merak_stage* S, hipStream_t s0) {
+    const AuxRef& own = S->aux;
     const bool capture = capturing(s0);
     std::unique_lock<std::mutex> lk(g_mu);
     if (!capture) {
-      for (const AuxRef& a : g_aux[dev])
-        if (a->served && a->caller == s0 && !a->busy) {
+      for (const AuxRef& a : g_aux[S->dev])
+        if (a->served && a->caller == s0 && !a->busy && (a == own || keep(S, a))) {
           ref_ = a;
           break;
         }
@@ -319,6 +323,15 @@ class AuxLoan {
   hipStream_t stream() const { return ref_->st; }
 
  private:
+  static bool keep(merak_stage* S, const AuxRef& a) {
+    if (std::find(S->borrowed.begin(), S->borrowed.end(), a) != S->borrowed.end()) return true;
+    try {
+      S->borrowed.push_back(a);
+    } catch (const std::bad_alloc&) {
+      return false;
+    }
+    return true;
+  }
   AuxRef ref_;
 };
 
@@ -765,7 +778,7 @@ int merak_stage_destroy(merak_stage_t S) {
     (void)hipEventDestroy(S->ev_rc[l][1]);
   }
   for (hipEvent_t ev : S->t_ev) (void)hipEventDestroy(ev);
-  delete S;  // and its stream, once no call has it on loan
+  delete S;  // and the streams that no other handle has used
   return MERAK_OK;
 }
 
@@ -885,7 +898,7 @@ int merak_stage_bwd(merak_stage_t S, const void* params, const void* dy, void* d
   const Dims& D = S->D;
   const size_t th = (size_t)D.T * D.h * D.esz;
   const size_t th_al = align_up(th, 256);
-  const AuxLoan loan(S->dev, S->aux, s0);
+  const AuxLoan loan(S, s0);
   const hipStream_t aux = loan.stream();
   S->state = ST_IDLE;  // consumed, also if a launch fails part-way
   TRY(fork(S, s0, s1));

@@ -1,0 +1,108 @@
+// The stage schedule's streams against a stand-in for the HIP runtime
+// (fake_hip.h): which calls may wait for which, and how long the library's
+// streams live.  `stream_check <scenario>` runs one of the scenarios below.
+#include <stdint.h>
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include <thread>
+#include <vector>
+
+#include "fake_hip.h"
+#include "merak_stage.h"
+
+#define EXPECT(c)                                                             \
+  do {                                                                        \
+    if (!(c)) {                                                               \
+      fprintf(stderr, "check failed at %s:%d: %s\n", __FILE__, __LINE__, #c); \
+      exit(1);                                                                \
+    }                                                                         \
+  } while (0)
+
+namespace {
+// Device memory is never touched on the host: any aligned address will do.
+void* dev(uintptr_t k) { return reinterpret_cast<void*>((uintptr_t)0x100000000 + k * 0x1000000); }
+
+merak_stage_config config() {
+  merak_stage_config c{};
+  c.n_blocks = 3;
+  c.hidden = 256;
+  c.n_heads = 4;
+  c.ffn = 1024;
+  c.seq_len = 128;
+  c.micro_batch = 4;
+  c.tp_degree = 1;
+  c.n_sub_microbatches = 2;
+  c.recompute_mask = 1;
+  c.dtype = MERAK_BF16;
+  c.ln_eps = 1e-5f;
+  return c;
+}
+
+struct Pair {
+  hipStream_t s0, s1;
+};
+Pair pair() { return {fake::caller_stream(), fake::caller_stream()}; }
+
+merak_stage_t create(int k) {
+  const merak_stage_config c = config();
+  size_t ws = 0, rc = 0;
+  EXPECT(merak_stage_workspace_bytes(&c, &ws, &rc) == MERAK_OK);
+  merak_stage_t h = nullptr;
+  EXPECT(merak_stage_create(&c, dev(100 + 2 * k), ws, dev(101 + 2 * k), rc, &h) == MERAK_OK);
+  return h;
+}
+
+void backward(merak_stage_t h, Pair p) {
+  EXPECT(merak_stage_bwd(h, dev(1), dev(2), dev(3), static_cast<float*>(dev(4)), 0, nullptr, p.s0, p.s1) == MERAK_OK);
+}
+void step(merak_stage_t h, Pair p) {
+  EXPECT(merak_stage_fwd(h, dev(1), dev(5), dev(6), nullptr, p.s0, p.s1) == MERAK_OK);
+  EXPECT(merak_stage_recompute(h, dev(1), p.s0, p.s1) == MERAK_OK);
+  backward(h, p);
+}
+
+// A handle is destroyed once its own work is done; another handle that has
+// used the same stream of the library keeps its queued work.
+void lifetime() {
+  merak_stage_t a = create(0), b = create(1);
+  const Pair x = pair();
+  step(a, x);
+  fake::run();
+  EXPECT(fake::idle(x.s0) && fake::idle(x.s1));
+  fake::hold(x.s0);
+  step(b, x);
+  fake::run();
+  EXPECT(merak_stage_destroy(a) == MERAK_OK);
+  EXPECT(fake::misuse() == 0);
+  fake::release(x.s0);
+  fake::run();
+  EXPECT(fake::idle(x.s0) && fake::idle(x.s1));
+  step(b, x);
+  fake::run();
+  EXPECT(fake::idle(x.s0) && fake::idle(x.s1));
+  EXPECT(merak_stage_destroy(b) == MERAK_OK);
+}
+
+const struct {
+  const char* name;
+  void (*run)();
+} kScenarios[] = {
+    {"lifetime", lifetime},
+};
+}  // namespace
+
+int main(int argc, char** argv) {
+  for (const auto& s : kScenarios)
+    if (argc == 2 && !strcmp(argv[1], s.name)) {
+      s.run();
+      // every scenario destroys its handles after their work
+      EXPECT(fake::misuse() == 0);
+      EXPECT(fake::live_streams() == 0 && fake::live_events() == 0);
+      printf("%s passed\n", s.name);
+      return 0;
+    }
+  fprintf(stderr, "no such scenario\n");
+  return 2;
+}
