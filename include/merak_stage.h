@@ -133,12 +133,13 @@ int merak_stage_workspace_bytes(const merak_stage_config* cfg, size_t* workspace
 /* Create a handle bound to a configuration and caller-owned device memory.
  * The workspace must hold at least *workspace_bytes and stays owned by the
  * caller; it must not be freed before merak_stage_destroy.  recompute_area may
- * be NULL when recompute_bytes is 0.  Needs the GPU (creates HIP events on the
- * current device).  On success *out receives the handle. */
+ * be NULL when recompute_bytes is 0.  Needs the GPU (creates HIP streams and
+ * events on the current device).  On success *out receives the handle. */
 int merak_stage_create(const merak_stage_config* cfg, void* workspace, size_t workspace_bytes,
                        void* recompute_area, size_t recompute_bytes, merak_stage_t* out);
 
-/* Destroy a handle (waits for nothing; the caller synchronises first). */
+/* Destroy a handle (waits for nothing; the caller synchronises this handle's work
+ * first, and no other's). */
 int merak_stage_destroy(merak_stage_t stage);
 
 /* Forward pass of the stage for one micro-batch.
@@ -181,7 +182,8 @@ int merak_stage_recompute(merak_stage_t stage, const void* params, void* stream0
  *                 AllReduces.
  * Weight gradients are computed per block over the whole micro-batch once all
  * its sub-micro-batches are done (deterministic; no floating-point atomics), on
- * a stream of the library that handles used on one caller stream share.
+ * a stream of the library that the handles used on one pair of streams share.
+ * A call on another pair never waits for what this pair's streams wait for.
  * MERAK_ERR_ORDER if no forward pass is pending, if the mask is nonzero and
  * merak_stage_recompute has not run since the forward pass, or if another
  * handle has recomputed into a shared recompute area since.  Consumes the

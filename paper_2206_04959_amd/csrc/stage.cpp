@@ -22,7 +22,6 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
-#include <condition_variable>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -215,7 +214,8 @@ bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
 // ---------------------------------------------------------------------------
 namespace {
 struct AuxStream;
-}
+constexpr int kAuxPairs = 4;  // pairs of caller streams that one handle keeps a stream for
+}  // namespace
 struct merak_stage {
   merak_stage_config cfg;
   Dims D;
@@ -225,8 +225,8 @@ struct merak_stage {
   char* ws;
   char* rc;
   int dev;  // the device current at creation
-  std::shared_ptr<AuxStream> aux;
-  std::vector<std::shared_ptr<AuxStream>> borrowed;  // other handles' streams its calls have used; under g_mu
+  std::shared_ptr<AuxStream> own, spare;          // for weight gradients (AuxStream below)
+  std::shared_ptr<AuxStream> pairs[kAuxPairs];    // streams of the pairs it has been used on; under g_mu, as spare
   hipEvent_t ev_fork, ev_s1, ev_j0, ev_j1, ev_aux, ev_dw[2];
   hipEvent_t ev_rc[kMaxBlocks][2];  // recompute of block l done on its two streams
   int state;  // 0 idle, 1 forward pending, 2 recomputed
@@ -245,38 +245,41 @@ enum { ST_IDLE = 0, ST_FWD = 1, ST_RECOMPUTED = 2 };
 std::mutex g_mu;
 std::map<void*, merak_stage*> g_rc_owner;  // recompute area -> handle that last filled it
 
-// The streams for weight gradients.  Every handle has one; a backward call uses
-// the stream of the device's oldest handle that last served the same caller
-// stream, so that calls made one after the other on one pair of streams, with
-// any handles, keep the weight gradients on one stream.  With each handle on its
-// own, the streams of a program with several handles exceed HIP's default of
-// four hardware queues, the library's stream then shares a queue with one of the
-// caller's, and the weight gradients run in turn with the chains instead of
-// beside them: with three handles the 8.3B-shaped step took 11.0 ms against
-// 10.0 with one, the 1.5B-shaped 13.3 against 11.9, the 2.5B-shaped 6.9 against
-// 5.7 and the 20B-shaped 15.8 against 14.9.
+// The streams for weight gradients.  A backward call on a pair of caller streams
+// uses the one stream of the library that serves this pair (and no other pair),
+// whichever handle it is made with.  With each handle on a stream of its own, the
+// streams of a program with several handles exceed HIP's default of four hardware
+// queues, the library's stream then shares a queue with one of the caller's, and
+// the weight gradients run in turn with the chains instead of beside them: with
+// three handles the 8.3B-shaped step took 11.0 ms against 10.0 with one, the
+// 1.5B-shaped 13.3 against 11.9, the 2.5B-shaped 6.9 against 5.7 and the
+// 20B-shaped 15.8 against 14.9.
 //
-// Only calls on one caller stream share: those wait for each other on it in any
-// case (a backward call ends with the caller's stream waiting for the weight
-// gradients, and the next one's start with what the caller's stream has reached),
-// so handles on streams of their own, where one may be held back by a receive
-// that another's work has to answer, never wait for each other.  Under graph
-// capture, and while another host thread's call has the shared stream, a call
-// uses its own handle's.  A handle keeps every stream that its calls have used
-// until it is destroyed, after its work: the handle a stream was made for may go
-// earlier, while another's weight gradients are still queued on it.
+// Sharing adds no wait.  Calls on one pair wait for each other in any case (a
+// backward call ends with stream0 waiting for the weight gradients, and the next
+// one's start with what stream0 has reached).  Calls on different pairs, where one
+// may be held back by a receive that another's work has to answer, never meet on a
+// stream, also where one handle has been used on both.  (A caller's stream is
+// destroyed after its work: a new one at its address finds the pair's stream idle.)
+//
+// A handle brings two streams: one that only its own calls use, and one that it
+// gives to the first pair it meets that no handle has served yet.  A pair's stream
+// lives until the last handle that has used it is destroyed, after its work.  A
+// call takes its handle's own stream where the pair's would not be the pair's
+// alone (under graph capture, while another host thread's call enqueues to it, and
+// for the per-thread stream, which is another stream in each thread) and where the
+// handle keeps kAuxPairs streams already.
 struct AuxStream {
   hipStream_t st = nullptr;
-  bool busy = false;          // lent to a call that is enqueueing; under g_mu
-  bool served = false;        // an eager call has used it, on caller stream `caller`
-  hipStream_t caller = nullptr;
+  int dev = 0;
+  hipStream_t s0 = nullptr, s1 = nullptr;  // the pair served
+  bool busy = false;                       // a call is enqueueing to it; under g_mu
   ~AuxStream() {
     if (st) (void)hipStreamDestroy(st);
   }
 };
 using AuxRef = std::shared_ptr<AuxStream>;
-std::map<int, std::vector<AuxRef>> g_aux;  // by device, in order of creation; under g_mu
-std::condition_variable g_aux_free;
+std::vector<AuxRef> g_pairs;  // streams that serve a pair; under g_mu
 
 bool capturing(hipStream_t st) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
@@ -285,54 +288,76 @@ bool capturing(hipStream_t st) {
   return true;
 }
 
-void drop_aux(int dev, const AuxRef& a) {
-  std::lock_guard<std::mutex> lk(g_mu);
-  std::vector<AuxRef>& all = g_aux[dev];
-  all.erase(std::find(all.begin(), all.end(), a));
+hipError_t make_aux(int dev, AuxRef* out) {
+  try {
+    *out = std::make_shared<AuxStream>();
+  } catch (const std::bad_alloc&) {
+    return hipErrorOutOfMemory;
+  }
+  (*out)->dev = dev;
+  return hipStreamCreateWithFlags(&(*out)->st, hipStreamNonBlocking);
 }
 
-// The stream lent to one backward call, for as long as it enqueues.
+// The stream that serves the pair, kept by S from now on; null if there is none
+// and S has none to give, or if S keeps as many as it may.
+AuxStream* pair_stream(merak_stage* S, hipStream_t s0, hipStream_t s1) {
+  auto serves = [&](const AuxRef& a) { return a && a->dev == S->dev && a->s0 == s0 && a->s1 == s1; };
+  AuxRef* slot = nullptr;
+  for (AuxRef& a : S->pairs) {
+    if (serves(a)) return a.get();
+    if (!a && !slot) slot = &a;
+  }
+  if (!slot) return nullptr;
+  const auto it = std::find_if(g_pairs.begin(), g_pairs.end(), serves);
+  if (it != g_pairs.end()) {
+    *slot = *it;
+  } else if (S->spare) {
+    try {
+      g_pairs.push_back(S->spare);
+    } catch (const std::bad_alloc&) {
+      return nullptr;
+    }
+    S->spare->s0 = s0;
+    S->spare->s1 = s1;
+    *slot = std::move(S->spare);
+  }
+  return slot->get();
+}
+
+// S keeps its pairs' streams no longer.  They are moved to `out`, to be let go of
+// outside the lock; one that no other handle keeps serves its pair no longer.
+void leave_pairs(merak_stage* S, AuxRef (&out)[kAuxPairs]) {
+  std::lock_guard<std::mutex> lk(g_mu);
+  for (int i = 0; i < kAuxPairs; ++i) {
+    out[i] = std::move(S->pairs[i]);
+    if (out[i] && out[i].use_count() == 2)  // this one and g_pairs'
+      g_pairs.erase(std::find(g_pairs.begin(), g_pairs.end(), out[i]));
+  }
+}
+
+// The stream of one backward call, for as long as it enqueues.
 class AuxLoan {
  public:
-  AuxLoan(merak_stage* S, hipStream_t s0) {
-    const AuxRef& own = S->aux;
-    const bool capture = capturing(s0);
-    std::unique_lock<std::mutex> lk(g_mu);
-    if (!capture) {
-      for (const AuxRef& a : g_aux[S->dev])
-        if (a->served && a->caller == s0 && !a->busy && (a == own || keep(S, a))) {
-          ref_ = a;
-          break;
-        }
-    }
-    if (!ref_) {
-      g_aux_free.wait(lk, [&] { return !own->busy; });  // at most for another call's enqueueing
-      ref_ = own;
-    }
-    ref_->served = !capture;  // a stream that a capture has taken is not lent
-    ref_->caller = s0;
-    ref_->busy = true;
+  AuxLoan(merak_stage* S, hipStream_t s0, hipStream_t s1) : aux_(S->own.get()) {
+    int dev = -1;
+    if (s0 == hipStreamPerThread || s1 == hipStreamPerThread || capturing(s0)) return;
+    if (hipGetDevice(&dev) != hipSuccess || dev != S->dev) return;  // the null stream is another one there
+    std::lock_guard<std::mutex> lk(g_mu);
+    AuxStream* a = pair_stream(S, s0, s1);
+    if (!a || a->busy) return;
+    aux_ = a;
+    aux_->busy = true;
   }
   ~AuxLoan() {
     std::lock_guard<std::mutex> lk(g_mu);
-    ref_->busy = false;
-    g_aux_free.notify_all();
+    aux_->busy = false;
   }
   AuxLoan(const AuxLoan&) = delete;
   AuxLoan& operator=(const AuxLoan&) = delete;
-  hipStream_t stream() const { return ref_->st; }
+  hipStream_t stream() const { return aux_->st; }
 
  private:
-  static bool keep(merak_stage* S, const AuxRef& a) {
-    if (std::find(S->borrowed.begin(), S->borrowed.end(), a) != S->borrowed.end()) return true;
-    try {
-      S->borrowed.push_back(a);
-    } catch (const std::bad_alloc&) {
-      return false;
-    }
-    return true;
-  }
-  AuxRef ref_;
+  AuxStream* aux_;
 };
 
 char* block_input(merak_stage* S, int l) {
@@ -718,19 +743,8 @@ int merak_stage_create(const merak_stage_config* cfg, void* workspace, size_t wo
   S->t_count = 0;
   S->t_overflow = false;
   hipError_t e = hipGetDevice(&S->dev);
-  if (e != hipSuccess) {
-    delete S;
-    return MERAK_ERR_HIP;
-  }
-  try {
-    S->aux = std::make_shared<AuxStream>();
-    std::lock_guard<std::mutex> lk(g_mu);
-    g_aux[S->dev].push_back(S->aux);  // lent to no other handle before this one's first backward call
-  } catch (const std::bad_alloc&) {
-    delete S;
-    return MERAK_ERR_INVALID_ARG;
-  }
-  e = hipStreamCreateWithFlags(&S->aux->st, hipStreamNonBlocking);
+  if (e == hipSuccess) e = make_aux(S->dev, &S->own);
+  if (e == hipSuccess) e = make_aux(S->dev, &S->spare);
   hipEvent_t* evs[] = {&S->ev_fork, &S->ev_s1, &S->ev_j0, &S->ev_j1, &S->ev_aux, &S->ev_dw[0], &S->ev_dw[1]};
   int made = 0;
   for (hipEvent_t* ev : evs) {
@@ -755,7 +769,6 @@ int merak_stage_create(const merak_stage_config* cfg, void* workspace, size_t wo
       (void)hipEventDestroy(S->ev_rc[l][0]);
       (void)hipEventDestroy(S->ev_rc[l][1]);
     }
-    drop_aux(S->dev, S->aux);
     delete S;
     return MERAK_ERR_HIP;
   }
@@ -770,7 +783,8 @@ int merak_stage_destroy(merak_stage_t S) {
     for (auto it = g_rc_owner.begin(); it != g_rc_owner.end();)
       it = (it->second == S) ? g_rc_owner.erase(it) : std::next(it);
   }
-  drop_aux(S->dev, S->aux);
+  AuxRef pairs[kAuxPairs];
+  leave_pairs(S, pairs);
   hipEvent_t evs[] = {S->ev_fork, S->ev_s1, S->ev_j0, S->ev_j1, S->ev_aux, S->ev_dw[0], S->ev_dw[1]};
   for (hipEvent_t ev : evs) (void)hipEventDestroy(ev);
   for (int l = 0; l < S->D.L; ++l) {
@@ -778,7 +792,7 @@ int merak_stage_destroy(merak_stage_t S) {
     (void)hipEventDestroy(S->ev_rc[l][1]);
   }
   for (hipEvent_t ev : S->t_ev) (void)hipEventDestroy(ev);
-  delete S;  // and the streams that no other handle has used
+  delete S;
   return MERAK_OK;
 }
 
@@ -898,7 +912,7 @@ int merak_stage_bwd(merak_stage_t S, const void* params, const void* dy, void* d
   const Dims& D = S->D;
   const size_t th = (size_t)D.T * D.h * D.esz;
   const size_t th_al = align_up(th, 256);
-  const AuxLoan loan(S, s0);
+  const AuxLoan loan(S, s0, s1);
   const hipStream_t aux = loan.stream();
   S->state = ST_IDLE;  // consumed, also if a launch fails part-way
   TRY(fork(S, s0, s1));

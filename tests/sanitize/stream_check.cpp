@@ -85,11 +85,46 @@ void lifetime() {
   EXPECT(merak_stage_destroy(b) == MERAK_OK);
 }
 
+// Calls on one pair of caller streams never wait for what another pair's streams
+// wait for, also where a handle has used both.
+void moved() {
+  merak_stage_t a = create(0), b = create(1), c = create(2);
+  const Pair x = pair(), y = pair(), z = pair();
+  step(a, x);
+  step(b, x);
+  fake::run();
+  fake::hold(x.s0);
+  step(b, x);  // waits on x
+  step(a, y);  // and what it has to receive, a sends on y
+  step(c, z);
+  fake::run();
+  EXPECT(!fake::idle(x.s0));
+  EXPECT(fake::idle(y.s0) && fake::idle(y.s1));
+  EXPECT(fake::idle(z.s0) && fake::idle(z.s1));
+  // the other way round, and with only the second stream held back
+  fake::release(x.s0);
+  fake::run();
+  EXPECT(fake::idle(x.s0));
+  fake::hold(y.s1);
+  step(a, y);
+  step(c, y);
+  step(b, z);
+  step(b, x);
+  fake::run();
+  EXPECT(!fake::idle(y.s0));
+  EXPECT(fake::idle(x.s0) && fake::idle(z.s0));
+  fake::release(y.s1);
+  fake::run();
+  EXPECT(fake::idle(y.s0) && fake::idle(y.s1));
+  for (merak_stage_t h : {a, b, c}) EXPECT(merak_stage_destroy(h) == MERAK_OK);
+}
+
 const struct {
   const char* name;
   void (*run)();
 } kScenarios[] = {
     {"lifetime", lifetime},
+    {"moved", moved},
 };
 }  // namespace
 

@@ -38,6 +38,6 @@ def _run(exe, scenario):
     assert f"{scenario} passed" in r.stdout
 
 
-@pytest.mark.parametrize("scenario", ["lifetime"])
+@pytest.mark.parametrize("scenario", ["lifetime", "moved"])
 def test_stage_streams(checked, scenario):
     _run(checked, scenario)
