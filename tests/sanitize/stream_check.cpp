@@ -119,12 +119,124 @@ void moved() {
   for (merak_stage_t h : {a, b, c}) EXPECT(merak_stage_destroy(h) == MERAK_OK);
 }
 
+// The library's streams that took kernels since the last call.
+std::vector<hipStream_t> aux_streams(std::vector<Pair> callers) {
+  std::vector<hipStream_t> v;
+  for (hipStream_t s : fake::launched_on()) {
+    bool caller = false;
+    for (const Pair& p : callers) caller |= s == p.s0 || s == p.s1;
+    if (!caller) v.push_back(s);
+  }
+  return v;
+}
+
+// Handles on one pair share a stream; under capture each uses one that no other
+// call uses, before, during or after.
+void captured() {
+  merak_stage_t h[3] = {create(0), create(1), create(2)};
+  const Pair x = pair(), y = pair();
+  aux_streams({});
+  for (merak_stage_t k : h) step(k, x);
+  const std::vector<hipStream_t> shared = aux_streams({x});
+  EXPECT(shared.size() == 1);
+  fake::run();
+  fake::capture(x.s0, true);
+  std::vector<hipStream_t> own;
+  for (int i = 0; i < 2; ++i) {
+    step(h[i], x);
+    const std::vector<hipStream_t> a = aux_streams({x});
+    EXPECT(a.size() == 1 && a[0] != shared[0]);
+    for (hipStream_t o : own) EXPECT(a[0] != o);
+    own.push_back(a[0]);
+  }
+  step(h[2], y);  // eager, on other streams, meanwhile
+  const std::vector<hipStream_t> other = aux_streams({y});
+  EXPECT(other.size() == 1 && other[0] != shared[0] && other[0] != own[0] && other[0] != own[1]);
+  fake::capture(x.s0, false);
+  for (merak_stage_t k : h) step(k, x);
+  EXPECT(aux_streams({x}) == shared);
+  fake::run();
+  for (merak_stage_t k : h) EXPECT(merak_stage_destroy(k) == MERAK_OK);
+}
+
+// Host threads at once, each with handles of its own: on pairs of their own, and
+// all on one pair.
+void threads() {
+  const Pair shared = pair();
+  for (bool one_pair : {false, true}) {
+    std::vector<std::thread> ts;
+    for (int t = 0; t < 4; ++t)
+      ts.emplace_back([=] {
+        const Pair mine = one_pair ? shared : pair();
+        for (int round = 0; round < 20; ++round) {
+          merak_stage_t a = create(2 * t), b = create(2 * t + 1);
+          for (int i = 0; i < 5; ++i) {
+            step(a, mine);
+            step(b, mine);
+          }
+          fake::run();
+          EXPECT(merak_stage_destroy(a) == MERAK_OK);
+          step(b, mine);
+          fake::run();
+          EXPECT(merak_stage_destroy(b) == MERAK_OK);
+        }
+      });
+    for (std::thread& t : ts) t.join();
+    fake::run();
+    EXPECT(fake::idle(shared.s0) && fake::idle(shared.s1));
+  }
+}
+
+// A handle on more pairs than it keeps streams for, on the null stream, and on the
+// per-thread stream (never shared: its value names another stream in each thread).
+void many_pairs() {
+  merak_stage_t a = create(0), b = create(1);
+  std::vector<Pair> ps;
+  for (int i = 0; i < 12; ++i) ps.push_back(pair());
+  ps.push_back({nullptr, nullptr});
+  for (int turn = 0; turn < 2; ++turn)
+    for (const Pair& p : ps) {
+      step(a, p);
+      step(b, p);
+      fake::run();
+      EXPECT(fake::idle(p.s0) && fake::idle(p.s1));
+    }
+  EXPECT(fake::live_streams() <= 4);
+  const Pair per_thread{hipStreamPerThread, hipStreamPerThread};
+  aux_streams({});
+  step(a, per_thread);
+  const std::vector<hipStream_t> sa = aux_streams({per_thread});
+  step(b, per_thread);
+  const std::vector<hipStream_t> sb = aux_streams({per_thread});
+  EXPECT(sa.size() == 1 && sb.size() == 1 && sa[0] != sb[0]);
+  fake::run();
+  for (merak_stage_t h : {a, b}) EXPECT(merak_stage_destroy(h) == MERAK_OK);
+}
+
+// A creation that fails part-way leaves nothing behind.
+void failed_create() {
+  const merak_stage_config c = config();
+  size_t ws = 0, rc = 0;
+  EXPECT(merak_stage_workspace_bytes(&c, &ws, &rc) == MERAK_OK);
+  for (int n = 0; n < 2; ++n) {
+    fake::fail_stream_create_after(n);
+    merak_stage_t h = nullptr;
+    EXPECT(merak_stage_create(&c, dev(100), ws, dev(101), rc, &h) == MERAK_ERR_HIP && h == nullptr);
+    EXPECT(fake::live_streams() == 0 && fake::live_events() == 0);
+  }
+  fake::fail_stream_create_after(-1);
+}
+
 const struct {
   const char* name;
   void (*run)();
 } kScenarios[] = {
     {"lifetime", lifetime},
     {"moved", moved},
+    {"captured", captured},
+    {"threads", threads},
+    {"many_pairs", many_pairs},
+    {"failed_create", failed_create},
 };
 }  // namespace
 

@@ -243,11 +243,12 @@ SHARED = synth.StageShape("shared", n_blocks=3, hidden=256, n_heads=4, ffn=1024,
 
 @pytest.mark.parametrize("pairs", [(0, 0, 0), (0, 1, 2), (0, 0, 1)])
 def test_backward_calls_of_several_handles(pairs):
-    """Backward calls on one caller stream share a handle's weight-gradient
-    stream: handles used in turn on one pair of streams, on pairs of their own
-    and on both, handles that then change pairs, and a handle used after the one
-    that owns the stream was destroyed, each give the bits of a handle used
-    alone.  (pairs: which pair of streams each handle runs on.)"""
+    """Backward calls on one pair of caller streams share a weight-gradient
+    stream: handles used in turn on one pair, on pairs of their own and on both,
+    handles that then change pairs, and a handle used after the one that brought
+    the stream was destroyed, each give the bits of a handle used alone.  (pairs:
+    which pair of streams each handle runs on.)  Which calls may wait for which is
+    checked in test_host_streams.py."""
     torch = need_gpu()
     print(f"[several handles] pairs {pairs}", flush=True)
     shapes = [SHARED.replace(seed=77 + i) for i in range(3)]
@@ -277,8 +278,11 @@ def test_backward_calls_of_several_handles(pairs):
 
 # The first run of the next two tests, with an earlier form of the stream
 # sharing, ended in a segmentation fault of the host process; which of the two
-# it was, and why, has not been shown.  Host threads at once and graph capture
-# of whole steps are not covered elsewhere.
+# it was, and why, has not been shown.  That form is gone: under capture and on
+# pairs of streams of its own a handle's calls use a stream that no other call
+# uses.  The library's host code on both paths runs in test_host_streams.py,
+# against a stand-in for the HIP runtime, without a finding of the address and
+# thread sanitizers; the HIP runtime's part is not covered.
 _UNSHOWN = "ended the process with a segmentation fault in its first run; the cause has not been shown"
 
 

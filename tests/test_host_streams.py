@@ -1,7 +1,8 @@
 """Streams and events of the stage schedule, without a GPU:
 tests/sanitize/stream_check.cpp runs the library's host code against a stand-in
 for the HIP runtime (fake_hip.cpp) that models streams as queues, under
-AddressSanitizer and UndefinedBehaviorSanitizer."""
+AddressSanitizer and UndefinedBehaviorSanitizer, and the host-thread scenario
+under ThreadSanitizer."""
 import os
 import shutil
 import subprocess
@@ -38,6 +39,14 @@ def _run(exe, scenario):
     assert f"{scenario} passed" in r.stdout
 
 
-@pytest.mark.parametrize("scenario", ["lifetime", "moved"])
+@pytest.mark.parametrize("scenario", ["lifetime", "moved", "captured", "threads", "many_pairs", "failed_create"])
 def test_stage_streams(checked, scenario):
     _run(checked, scenario)
+
+
+def test_stage_streams_from_threads_race_free(tmp_path):
+    exe = _build(tmp_path, "-fsanitize=thread")
+    r = subprocess.run([exe, "failed_create"], capture_output=True, text=True, timeout=60)
+    if "unexpected memory mapping" in r.stderr:
+        pytest.skip("ThreadSanitizer does not run on this kernel's address layout")
+    _run(exe, "threads")
