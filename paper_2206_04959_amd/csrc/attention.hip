@@ -547,13 +547,6 @@ __global__ void __launch_bounds__(256, (D <= 96 ? 2 : 1))
       fb[ks] = fr.row(dOt, ks);
       __builtin_amdgcn_sched_barrier(0);
     }
-    // p[r]: query 64 (kt + t) + 32 qh + (r/4)*8 + 4*hf + r%4, key `key`.
-    if (t == 0) {  // the only tiles with queries before a key
-      const int lim = key - (kt * 64 + qh * 32) - hf * 4;
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if ((r >> 2) * 8 + (r & 3) < lim) p[r] = -INFINITY;
-    }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
@@ -564,6 +557,15 @@ __global__ void __launch_bounds__(256, (D <= 96 ? 2 : 1))
         p[r] = pinned(__builtin_amdgcn_exp2f(fmaf(p[r], scale_log2, -ls[r >> 2][r & 3])));
       __builtin_amdgcn_sched_barrier(0);
     }
+    // p[r]: query 64 (kt + t) + 32 qh + (r/4)*8 + 4*hf + r%4, key `key`.  Masked
+    // after the exponential, so that a query's non-finite lse reaches no key after it.
+    if (t == 0) {  // the only tiles with queries before a key
+      const int lim = key - (kt * 64 + qh * 32) - hf * 4;
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if ((r >> 2) * 8 + (r & 3) < lim) p[r] = 0.0f;
+    }
+    __builtin_amdgcn_sched_barrier(0);
     const bf16x8_t pb[2] = {cvt8(p, 0), cvt8(p, 8)};
 #pragma unroll
     for (int g = 0; g < 4; ++g) de[g] = *reinterpret_cast<const f32x4_t*>(vec + 32 + g * 8);
