@@ -835,10 +835,10 @@ __device__ __forceinline__ void accumulate_f32(const float* t, size_t ld, const 
 template <int D>
 constexpr size_t f32_lds_bytes() { return (size_t)4 * D * 32 * 4 + 4 * 64 * 4; }
 
-// Sum of the four waves' accumulators, times f, to rows of stride ld (`out`:
-// the lane's row, first column).
+// Sum of the four waves' accumulators, times f, to `out` (the lane's row, first
+// column).  Returns whether one of the lane's results is not finite.
 template <int D>
-__device__ __forceinline__ void merge_f32(char* smem, const f32x16_t (&acc)[D / 32], float f, float* out, int wave,
+__device__ __forceinline__ bool merge_f32(char* smem, const f32x16_t (&acc)[D / 32], float f, float* out, int wave,
                                           int lane) {
   float* part = reinterpret_cast<float*>(smem);
   __syncthreads();
@@ -847,6 +847,7 @@ __device__ __forceinline__ void merge_f32(char* smem, const f32x16_t (&acc)[D / 
 #pragma unroll
     for (int r = 0; r < 16; ++r) part[((wave * (D / 32) + dt) * 16 + r) * 64 + lane] = acc[dt][r];
   __syncthreads();
+  bool odd = false;
 #pragma unroll
   for (int dt = 0; dt < D / 32; ++dt) {  // wave w: registers 4 w .. 4 w + 3 of every column group
     float v[4];
@@ -856,9 +857,41 @@ __device__ __forceinline__ void merge_f32(char* smem, const f32x16_t (&acc)[D / 
 #pragma unroll
       for (int w = 0; w < 4; ++w) v[e] += part[((w * (D / 32) + dt) * 16 + wave * 4 + e) * 64 + lane];
       v[e] *= f;
+      odd |= !(fabsf(v[e]) < INFINITY);
     }
     store4(out + dt * 32 + wave * 8 + (lane >> 5) * 4, v);
   }
+  return odd;
+}
+
+// Results that are not finite.  The products take masked terms as 0 times a value
+// of the diagonal tile, which is NaN where that value is not finite: a token's NaN
+// would reach rows that the mask keeps from it.  So a lane whose results (D / 32
+// groups of 4 columns, `col` the first) are not all finite forms them once more,
+// term by term over the rows that it does see, and replaces those that were not.
+// Nothing of it runs on finite results; a test of the values in the products made
+// the kernels 15-20% slower.
+template <int D>
+__device__ __forceinline__ void replace_f32(float* out, const f32x4_t (&v)[D / 32], float f) {
+#pragma unroll
+  for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (!(fabsf(out[dt * 32 + e]) < INFINITY)) out[dt * 32 + e] = v[dt][e] * f;
+}
+
+template <int D>
+__device__ __forceinline__ float row_dot_f32(const float* a, const float* b) {
+  float s = 0.0f;
+#pragma unroll 4
+  for (int d = 0; d < D; ++d) s += a[d] * b[d];
+  return s;
+}
+
+template <int D>
+__device__ __forceinline__ void add_f32(f32x4_t (&acc)[D / 32], float a, float p, const float* v) {
+#pragma unroll
+  for (int dt = 0; dt < D / 32; ++dt) acc[dt] = acc[dt] * a + p * *reinterpret_cast<const f32x4_t*>(v + dt * 32);
 }
 
 template <int D>
@@ -925,17 +958,32 @@ __global__ void __launch_bounds__(256) attn_fwd_f32(int S, int H, int Bm, int ms
   for (int dt = 0; dt < D / 32; ++dt)
 #pragma unroll
     for (int r = 0; r < 16; ++r) oacc[dt][r] *= a;
-  merge_f32<D>(smem, oacc, 1.0f, o + (((size_t)b * S + q) * H + hh) * D, wave, lane);
+  float* orow = o + (((size_t)b * S + q) * H + hh) * D;
+  const bool odd = merge_f32<D>(smem, oacc, 1.0f, orow, wave, lane);
   if (wave == 0 && hf == 0) lse[((size_t)b * H + hh) * S + q] = mt + logf(lt);
+  if (!odd) return;
+  const int col = wave * 8 + hf * 4;
+  f32x4_t acc[D / 32] = {};
+  m = -INFINITY;
+  l = 0.0f;
+  for (int j = 0; j <= q && l == l; ++j) {
+    const float s = row_dot_f32<D>(base + (size_t)q * rs, Kp + (size_t)j * rs) * scale;
+    const float mn = fmaxf(m, s), alpha = expf(m - mn), p = expf(s - mn);
+    l = l * alpha + p;
+    add_f32<D>(acc, alpha, p, Vp + (size_t)j * rs + col);
+    m = mn;
+  }
+  replace_f32<D>(orow + col, acc, 1.0f / l);
 }
 
 // dQ, and delta = dO . O of its rows for the dK/dV kernel launched after it.
+// (At most two waves per SIMD: with three at d = 64 the loads are issued later, 35.0
+// against 33.3 us for the backward of 1 x 256 x 4 heads.)
 template <int D>
-__global__ void __launch_bounds__(256) attn_bwd_dq_f32(int S, int H, int Bm, int mstride,
-                                                       const float* __restrict__ qkv, const float* __restrict__ o,
-                                                       const float* __restrict__ dout, const float* __restrict__ lse,
-                                                       float* __restrict__ delta, float* __restrict__ dqkv,
-                                                       float scale) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2)))
+    attn_bwd_dq_f32(int S, int H, int Bm, int mstride, const float* __restrict__ qkv, const float* __restrict__ o,
+                    const float* __restrict__ dout, const float* __restrict__ lse, float* __restrict__ delta,
+                    float* __restrict__ dqkv, float scale) {
   extern __shared__ __align__(16) char smem[];
   const int b = seq_index(blockIdx.x / H, Bm, mstride), hh = blockIdx.x % H;
   const int qt = gridDim.y - 1 - blockIdx.y;
@@ -977,7 +1025,17 @@ __global__ void __launch_bounds__(256) attn_bwd_dq_f32(int S, int H, int Bm, int
     }
     accumulate_f32<D>(Kp + (size_t)(t * 32 + hf * 4) * rs + l32, rs, p, dq);
   }
-  merge_f32<D>(smem, dq, scale, dqkv + ((size_t)b * S + q) * rs + (size_t)hh * D, wave, lane);
+  float* qo = dqkv + ((size_t)b * S + q) * rs + (size_t)hh * D;
+  if (!merge_f32<D>(smem, dq, scale, qo, wave, lane)) return;
+  const int col = wave * 8 + hf * 4;
+  f32x4_t acc[D / 32] = {};
+  float ds = 0.0f;
+  for (int j = 0; j <= q && ds == ds; ++j) {
+    const float s = row_dot_f32<D>(base + (size_t)q * rs, Kp + (size_t)j * rs);
+    ds = expf(s * scale - L) * (row_dot_f32<D>(dout + row, Vp + (size_t)j * rs) - del);
+    add_f32<D>(acc, 1.0f, ds, Kp + (size_t)j * rs + col);
+  }
+  replace_f32<D>(qo + col, acc, scale);
 }
 
 template <int D>
@@ -1022,8 +1080,22 @@ __global__ void __launch_bounds__(256) attn_bwd_dkdv_f32(int S, int H, int Bm, i
     accumulate_f32<D>(base + (size_t)(t * 32 + hf * 4) * rs + l32, rs, dp, dk);
   }
   float* ko = dqkv + ((size_t)b * S + key) * rs + (size_t)H * D + (size_t)hh * D;
-  merge_f32<D>(smem, dk, scale, ko, wave, lane);
-  merge_f32<D>(smem, dv, 1.0f, ko + (size_t)H * D, wave, lane);
+  float* vo = ko + (size_t)H * D;
+  const bool odd_k = merge_f32<D>(smem, dk, scale, ko, wave, lane);
+  const bool odd_v = merge_f32<D>(smem, dv, 1.0f, vo, wave, lane);
+  if (!odd_k && !odd_v) return;
+  const int col = wave * 8 + hf * 4;
+  const float* kr = base + (size_t)key * rs + (size_t)H * D;
+  f32x4_t ak[D / 32] = {}, av[D / 32] = {};
+  float p = 0.0f;
+  for (int i = key; i < S && p == p; ++i) {
+    const float *qr = base + (size_t)i * rs, *dor = dop + (size_t)i * ors;
+    p = expf(row_dot_f32<D>(qr, kr) * scale - lp[i]);
+    add_f32<D>(av, 1.0f, p, dor + col);
+    add_f32<D>(ak, 1.0f, p * (row_dot_f32<D>(dor, kr + (size_t)H * D) - dlp[i]), qr + col);
+  }
+  replace_f32<D>(ko + col, ak, scale);
+  replace_f32<D>(vo + col, av, 1.0f);
 }
 
 // ---------------------------------------------------------------------------

@@ -48,3 +48,49 @@ def test_row_statistic_nan_reaches_no_masked_key(d, dtype, row):
         assert torch.equal(nv[row + 1:], dv[row + 1:]) and torch.equal(nk[row + 1:], dk[row + 1:])
         assert torch.equal(nq[:row], dq[:row]) and torch.equal(nq[row + 1:], dq[row + 1:])
         assert not torch.isfinite(nq[row]).any() and not torch.isfinite(nv[row]).any()
+
+
+def _close(got, want):
+    """fp32 sums of up to 192 terms in another order, as for the finite cases of
+    test_gpu_kernels.py; a NaN fails."""
+    return bool((got - want).abs().max() <= 1e-5 * want.abs().max())
+
+
+# a row in the middle of a 32-row tile, the first and the last of one
+@pytest.mark.parametrize("bad", ["nan", "inf"])
+@pytest.mark.parametrize("row", [74, 64, 95])
+@pytest.mark.parametrize("d", [64, 96, 128])
+def test_fp32_token_reaches_only_rows_that_see_it(d, row, bad):
+    """fp32: one non-finite element in a token's q, k, v or dO.  The rows before the
+    token (for the gradients of k and v: after it) are those of the clean call."""
+    torch = need_gpu()
+    print(f"[non-finite] fp32 token d={d} row={row} {bad}", flush=True)
+    qkv, do, o, lse = _call(torch, d, torch.float32)
+    dq, dk, dv = _backward(torch, d, qkv, do, o, lse)
+    for which in range(3):
+        poisoned = qkv.clone()
+        poisoned[0, row, which, :, d // 3] = float(bad)
+        o1, lse1 = torch.empty_like(o), torch.empty_like(lse)
+        B.attention_fwd(poisoned, o1, lse1, 1, SEQ, HEADS, d)
+        torch.cuda.synchronize()
+        assert _close(o1[0, :row], o[0, :row]) and torch.equal(lse1[0, :, :row], lse[0, :, :row])
+        sees = torch.isfinite(o1[0, row:]).all(-1).all(-1)
+        if bad == "nan" or which == 2:  # (an infinite score can also be a weight of exactly 0)
+            assert not sees[0] and (which == 0 or not sees.any())
+        if which == 2:  # a value: one column only
+            keep = [c for c in range(d) if c != d // 3]
+            assert torch.equal(o1[..., keep], o[..., keep])
+        nq, nk, nv = _backward(torch, d, poisoned, do, o, lse)
+        assert _close(nq[:row], dq[:row])
+        assert _close(nk[row + 1:], dk[row + 1:]) and _close(nv[row + 1:], dv[row + 1:])
+        if which == 0:  # a query: only its own dq, and dk and dv of the keys up to it
+            assert _close(nq[row + 1:], dq[row + 1:]) and not torch.isfinite(nk[: row + 1]).all()
+        else:  # a key or value: only its own dk and dv, and dq of the queries from it on
+            assert _close(nk[:row], dk[:row]) and _close(nv[:row], dv[:row])
+            assert not torch.isfinite(nq[row:]).all()
+    bad_do = do.clone()
+    bad_do[0, row, :, d // 3] = float(bad)
+    nq, nk, nv = _backward(torch, d, qkv, bad_do, o, lse)
+    assert _close(nq[:row], dq[:row]) and _close(nq[row + 1:], dq[row + 1:])
+    assert _close(nk[row + 1:], dk[row + 1:]) and _close(nv[row + 1:], dv[row + 1:])
+    assert not torch.isfinite(nv[: row + 1, :, d // 3]).any()
