@@ -144,14 +144,14 @@ __global__ void __launch_bounds__(256) ln_bwd_kernel(int rows, int mrows, int ms
 // Segment/slice partial sums.  Mode 0: part0 = sum a.  Mode 1 (LayerNorm
 // parameters): part0 = sum a * xhat, part1 = sum a, with xhat rebuilt from x,
 // mean and rstd.  One launch covers up to kMaxColJobs reductions; workgroup
-// ranges are assigned to the jobs in order.
+// ranges are assigned to the jobs in order.  UNROLL rows of a wave are in flight.
 struct ColPartialBatch {
   ColPartialJob j[kMaxColJobs];
   int start[kMaxColJobs + 1];  // first workgroup of each job
   int n;
 };
 
-template <typename T, int MODE>
+template <typename T, int MODE, int UNROLL = 1>
 __device__ __forceinline__ void segment_partials(const ColPartialJob& J, int cx, int seg,
                                                  float (&red)[2][kRowsPerBlock][64 * 8]) {
   constexpr int NQ = MODE == 0 ? 1 : 2;
@@ -168,6 +168,7 @@ __device__ __forceinline__ void segment_partials(const ColPartialJob& J, int cx,
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[q][e] = 0.0f;
   if (c < J.cols) {
+#pragma unroll UNROLL
     for (int r = r0 + w; r < r1; r += kRowsPerBlock) {
       float v[8];
       load8(a + (size_t)r * J.cols + c, v);
@@ -229,11 +230,19 @@ __global__ void __launch_bounds__(256) segment_partials_kernel(ColPartialBatch b
 // bf16 moves 101 MB, 21.4 us (4.7 TB/s, the rate of a large copy); two launches
 // took 18.0 + 9.8 us there.  The whole call, with one launch for both final
 // sums: 34.5 -> 29.4 us, at 2048 x 1600 21.9 -> 11.7 us.
+//
+// Above 4096 columns the row workgroups' registers leave one or two waves per
+// SIMD, to the workgroups of the partial sums too, which then wait for one row at
+// a time: 8192 x 6144 in bf16 took 134 us, with the sums in a launch of their own
+// 128.  There they keep four rows (above 6144 columns eight) in flight: 115 us;
+// 8192 x 5120 112 -> 98, 12288 x 8192 372 -> 346.  At 4096 columns and fewer,
+// with three waves and more, short calls lose 3-5% by it.
 constexpr int kSegRowBlocks = kReduceRows / kRowsPerBlock;
 
 template <typename T, int CH>
 __global__ void __launch_bounds__(256) ln_bwd_full_kernel(ColPartialJob J, const T* __restrict__ gamma,
                                                           const T* __restrict__ dres, T* __restrict__ dx) {
+  constexpr int kUnroll = CH >= 16 ? 8 : CH >= 12 ? 4 : 1;
   __shared__ float red[2][kRowsPerBlock][64 * 8];
   const int ncx = (J.cols / 8 + 63) / 64, per = kSegRowBlocks + ncx;
   const int i = blockIdx.x >> 3, seg = (i / per) * 8 + (blockIdx.x & 7), k = i % per;
@@ -244,7 +253,7 @@ __global__ void __launch_bounds__(256) ln_bwd_full_kernel(ColPartialJob J, const
       ln_bwd_row<T, CH>(row, threadIdx.x & 63, J.cols, static_cast<const T*>(J.a), static_cast<const T*>(J.x), J.mean,
                         J.rstd, gamma, dres, dx);
   } else {
-    segment_partials<T, 1>(J, k - kSegRowBlocks, seg, red);
+    segment_partials<T, 1, kUnroll>(J, k - kSegRowBlocks, seg, red);
   }
 }
 

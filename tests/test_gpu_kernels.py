@@ -200,9 +200,11 @@ def test_layernorm_fwd_bwd(dtype, h):
 
 
 # one row; one segment of 64 rows and one row more; nine segments (one XCD gets
-# two of them) over widths of one, two and three 512-column slices
+# two of them) over widths of one, two and three 512-column slices; and the widths
+# whose sums keep four and eight rows in flight, with rows left over by either
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
-@pytest.mark.parametrize("rows,h", [(1, 64), (64, 512), (65, 520), (575, 1344)])
+@pytest.mark.parametrize("rows,h", [(1, 64), (64, 512), (65, 520), (575, 1344), (83, 4104), (575, 6144), (83, 6152),
+                                    (575, 8192)])
 def test_layernorm_bwd_one_launch_equals_parts(dtype, rows, h):
     """dx and the parameter sums made in one launch: dx against the oracle, the
     sums within fp32 rounding of the exact sums, and accumulate adds exactly the
