@@ -18,8 +18,8 @@
 // vector.  Workgroups are mapped to tiles so that each of the 8 XCDs works on
 // a compact block of neighbouring tiles (operand reuse in its own L2).
 //
-// fp32 check mode: fp32 matrix instructions on 32 x 32 tiles, the same layouts
-// and epilogues.
+// fp32 check mode: fp32 matrix instructions on 32 x 32 or 64 x 64 tiles, the same
+// layouts and epilogues.
 #include <atomic>
 #include <type_traits>
 
@@ -542,14 +542,15 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_mfma_kernel(GemmBatch batch
 
 // ---------------------------------------------------------------------------
 // fp32 check-mode kernel, on the fp32 matrix instruction (32x32x2: fp32 products
-// and sums).  A workgroup owns a 32 x 32 tile; its four waves split K and their
-// sums are added in wave order.  Operands go straight from global memory to
+// and sums).  A workgroup owns a tile of 32 NB x 32 NB; its four waves split K and
+// their sums are added in wave order.  Operands go straight from global memory to
 // registers, fetched one 16-deep group ahead: the product's k index h (= lane /
 // 32) of step j of chunk c is taken to mean k = 8 c + 4 h + j, so a lane reads
 // 16 bytes of a K-contiguous row (or four k-rows of an M- or N-contiguous
 // operand, 32 lanes side by side).  Small problems are bound by latency: a
 // 64 x 64 FMA tile, loaded and then used, took 20 us at 256 x 256 x 256 and 68 us
-// at 256 x 256 x 1024 (16 workgroups).
+// at 256 x 256 x 1024 (16 workgroups).  Large ones are bound by the operands' way
+// through L2; there NB = 2 (see run_f32).
 // ---------------------------------------------------------------------------
 template <bool TRANS>
 __device__ __forceinline__ void frag_f32(const float* p, int ld, f32x4_t (&f)[2]) {
@@ -564,56 +565,81 @@ __device__ __forceinline__ void frag_f32(const float* p, int ld, f32x4_t (&f)[2]
   }
 }
 
-template <bool A_T, bool B_T, int EPI>
+template <bool A_T, bool B_T, int EPI, int NB>
 __global__ void __launch_bounds__(256) gemm_f32_kernel(GemmBatch batch) {
+  constexpr int BT = 32 * NB;  // tile edge
   __shared__ float red[4][32][32 + 4];
   const int bid = blockIdx.x;
   int tile0;
   const GemmProblem p = select_problem(batch, bid, &tile0);
   const int tile = bid - tile0;
-  const int tiles_n = p.N / 32;
-  const int m0 = (tile / tiles_n) * 32, n0 = (tile % tiles_n) * 32;
+  const int tiles_n = p.N / BT;
+  const int m0 = (tile / tiles_n) * BT, n0 = (tile % tiles_n) * BT;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, hf = lane >> 5;
   const int kw = p.K / 4;  // a multiple of 16
   const size_t k0 = (size_t)wave * kw + 4 * hf;
   const float* a = reinterpret_cast<const float*>(p.a) + (A_T ? k0 * p.lda + m0 + l32 : (size_t)(m0 + l32) * p.lda + k0);
   const float* b = reinterpret_cast<const float*>(p.b) + (B_T ? k0 * p.ldb + n0 + l32 : (size_t)(n0 + l32) * p.ldb + k0);
   const size_t sa = A_T ? (size_t)16 * p.lda : 16, sb = B_T ? (size_t)16 * p.ldb : 16;
-  f32x16_t acc;
+  const size_t ra = A_T ? 32 : (size_t)32 * p.lda, rb = B_T ? 32 : (size_t)32 * p.ldb;  // to the next 32 rows
+  f32x16_t acc[NB][NB];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-  f32x4_t fa[2], fb[2];
-  frag_f32<A_T>(a, p.lda, fa);
-  frag_f32<B_T>(b, p.ldb, fb);
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+  f32x4_t fa[NB][2], fb[NB][2];
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    frag_f32<A_T>(a + i * ra, p.lda, fa[i]);
+    frag_f32<B_T>(b + i * rb, p.ldb, fb[i]);
+  }
   for (int k = 16; k <= kw; k += 16) {
-    f32x4_t na[2], nb[2];
+    f32x4_t na[NB][2], nb[NB][2];
     if (k < kw) {
       a += sa;
       b += sb;
     }
-    frag_f32<A_T>(a, p.lda, na);  // the last group again after the last step (unused)
-    frag_f32<B_T>(b, p.ldb, nb);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {  // the last group again after the last step (unused)
+      frag_f32<A_T>(a + i * ra, p.lda, na[i]);
+      frag_f32<B_T>(b + i * rb, p.ldb, nb[i]);
+    }
 #pragma unroll
     for (int c = 0; c < 2; ++c)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[c][j], fb[c][j], acc, 0, 0, 0);
+      for (int e = 0; e < 4; ++e)
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      fa[c] = na[c];
-      fb[c] = nb[c];
-    }
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+          for (int j = 0; j < NB; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][c][e], fb[j][c][e], acc[i][j], 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        fa[i][c] = na[i][c];
+        fb[i][c] = nb[i][c];
+      }
   }
-  // acc[r]: row (r/4)*8 + 4*hf + r%4, column l32.
-#pragma unroll
-  for (int r = 0; r < 16; ++r) red[wave][(r >> 2) * 8 + hf * 4 + (r & 3)][l32] = acc[r];
-  __syncthreads();
   const int row = tid >> 3, col = (tid & 7) * 4;
-  float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-  for (int w = 0; w < 4; ++w)
+  for (int i = 0; i < NB; ++i)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] += red[w][row][col + e];
-  epilogue4<float, EPI>(p, m0 + row, n0 + col, v);
+    for (int j = 0; j < NB; ++j) {
+      // acc[r]: row (r/4)*8 + 4*hf + r%4, column l32.
+      if (i + j > 0) __syncthreads();  // the sums before have been read
+#pragma unroll
+      for (int r = 0; r < 16; ++r) red[wave][(r >> 2) * 8 + hf * 4 + (r & 3)][l32] = acc[i][j][r];
+      __syncthreads();
+      float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int w = 0; w < 4; ++w)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] += red[w][row][col + e];
+      epilogue4<float, EPI>(p, m0 + 32 * i + row, n0 + 32 * j + col, v);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -638,17 +664,35 @@ static hipError_t run_mfma(GemmBatch& batch, hipStream_t stream) {
   return hipGetLastError();
 }
 
-template <bool AT, bool BT, int EPI>
-static hipError_t run_f32(GemmBatch& batch, hipStream_t stream) {
+template <bool AT, bool BT, int EPI, int NB>
+static hipError_t run_f32_tiles(GemmBatch& batch, hipStream_t stream) {
   int tiles = 0;
   for (int i = 0; i < batch.n_probs; ++i) {
     batch.tile_start[i] = tiles;
-    tiles += (batch.p[i].M / 32) * (batch.p[i].N / 32);
+    tiles += (batch.p[i].M / (32 * NB)) * (batch.p[i].N / (32 * NB));
   }
   for (int i = batch.n_probs; i <= kMaxGroup; ++i) batch.tile_start[i] = tiles;
   if (tiles == 0) return hipSuccess;
-  hipLaunchKernelGGL((gemm_f32_kernel<AT, BT, EPI>), dim3(tiles), dim3(256), 0, stream, batch);
+  hipLaunchKernelGGL((gemm_f32_kernel<AT, BT, EPI, NB>), dim3(tiles), dim3(256), 0, stream, batch);
   return hipGetLastError();
+}
+
+// 64 x 64 tiles where there are 800 of them (three rounds of 256 CUs), at A and B
+// of one layout: they fetch half the operand bytes.  Measured (us, 32 x 32 tiles ->
+// 64 x 64), M and K contiguous along one axis / the other: 8192 x 1024 x 512
+// 130 -> 97 / 127 -> 103, 4096 x 3072 x 3072 1043 -> 840 / 1034 -> 811, 2048 x 1600 x
+// 1600 153 -> 147 / 151 -> 140; but 3072 x 768 x 1024 (576 tiles) 70.6 -> 70.6 / 68.6 ->
+// 70.1 and 512 x 512 x 512 7.5 -> 13.0 / 7.5 -> 12.5.  With A contiguous along K and B
+// along N they are slower at every size (4096 x 3072 x 3072 840 -> 1013).  Both form
+// each sum in the same order.
+template <bool AT, bool BT, int EPI>
+static hipError_t run_f32(GemmBatch& batch, hipStream_t stream) {
+  if constexpr (AT == BT) {
+    long long tiles = 0;
+    for (int i = 0; i < batch.n_probs; ++i) tiles += (long long)(batch.p[i].M / 64) * (batch.p[i].N / 64);
+    if (tiles >= 800) return run_f32_tiles<AT, BT, EPI, 2>(batch, stream);
+  }
+  return run_f32_tiles<AT, BT, EPI, 1>(batch, stream);
 }
 
 // Tile shapes of the bf16 kernel: BM x BN with WM x WN waves and NS LDS stages.

@@ -94,6 +94,35 @@ def test_gemm_fp32_k_split(mnk, a_t, b_t):
     assert rel_err(B.to_host_f64(c), ref) < 1e-5
 
 
+@pytest.mark.parametrize("a_t,b_t", [(0, 0), (1, 1)])
+@pytest.mark.parametrize("epi", [B.EPI_STORE, B.EPI_BIAS, B.EPI_BIAS_GELU, B.EPI_BIAS_RESID, B.EPI_GELU_BWD, B.EPI_F32])
+def test_gemm_fp32_large_tiles(epi, a_t, b_t):
+    """fp32 kernel at the first number of 64x64 tiles that takes them (800), with
+    every epilogue: the bits of the same rows as a call with one row of tiles less,
+    which takes 32x32 tiles."""
+    torch = need_gpu()
+    M, N, K = 1280, 2560, 192
+    print(f"[gemm fp32 large] a_t={a_t} b_t={b_t} epi={epi}", flush=True)
+    a_p, _ = _rand((K, M) if a_t else (M, K), "fp32", 61)
+    b_p, _ = _rand((K, N) if b_t else (N, K), "fp32", 62)
+    bias, resid, aux0 = (_dev(_rand(s, "fp32", i)[0]) for i, s in ((63, (N,)), (64, (M, N)), (65, (M, N))))
+    a, b, out = _dev(a_p), _dev(b_p), []
+    for m in (M, M - 64):
+        c, aux = torch.full((m, N), 0.5, device="cuda"), aux0[:m].clone()
+        B.gemm(a, b, c, m, N, K, a_trans=a_t, b_trans=b_t, lda=M if a_t else K, epilogue=epi,
+               bias=bias if epi in (B.EPI_BIAS, B.EPI_BIAS_GELU, B.EPI_BIAS_RESID) else None,
+               resid=resid if epi == B.EPI_BIAS_RESID else None,
+               aux=aux if epi in (B.EPI_BIAS_GELU, B.EPI_BIAS_RESID, B.EPI_GELU_BWD) else None,
+               accumulate=epi == B.EPI_F32)
+        out.append((c, aux))
+    torch.cuda.synchronize()
+    assert torch.equal(out[0][0][:M - 64], out[1][0]) and torch.equal(out[0][1][:M - 64], out[1][1])
+    if epi == B.EPI_STORE:  # and the values of the last rows
+        A, Bm = a_p.astype(np.float64), b_p.astype(np.float64)
+        ref = (A.T if a_t else A)[M - 64:] @ (Bm if b_t else Bm.T)
+        assert rel_err(out[0][0][M - 64:].cpu().numpy(), ref) < 1e-5
+
+
 # (M, N, K) for which the choice for a lone launch is 64x128 (or 128x128 where A
 # is read transposed), 128x128, 192x128, 128x192 and 256x128 tiles, each with
 # ragged last tiles and more K stages than the ring holds; and one K stage.
