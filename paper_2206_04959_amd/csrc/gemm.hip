@@ -565,7 +565,7 @@ __device__ __forceinline__ void frag_f32(const float* p, int ld, f32x4_t (&f)[2]
   }
 }
 
-template <bool A_T, bool B_T, int EPI, int NB>
+template <int NB, bool A_T, bool B_T, int EPI>
 __global__ void __launch_bounds__(256) gemm_f32_kernel(GemmBatch batch) {
   constexpr int BT = 32 * NB;  // tile edge
   __shared__ float red[4][32][32 + 4];
@@ -664,7 +664,7 @@ static hipError_t run_mfma(GemmBatch& batch, hipStream_t stream) {
   return hipGetLastError();
 }
 
-template <bool AT, bool BT, int EPI, int NB>
+template <int NB, bool AT, bool BT, int EPI>
 static hipError_t run_f32_tiles(GemmBatch& batch, hipStream_t stream) {
   int tiles = 0;
   for (int i = 0; i < batch.n_probs; ++i) {
@@ -673,7 +673,7 @@ static hipError_t run_f32_tiles(GemmBatch& batch, hipStream_t stream) {
   }
   for (int i = batch.n_probs; i <= kMaxGroup; ++i) batch.tile_start[i] = tiles;
   if (tiles == 0) return hipSuccess;
-  hipLaunchKernelGGL((gemm_f32_kernel<AT, BT, EPI, NB>), dim3(tiles), dim3(256), 0, stream, batch);
+  hipLaunchKernelGGL((gemm_f32_kernel<NB, AT, BT, EPI>), dim3(tiles), dim3(256), 0, stream, batch);
   return hipGetLastError();
 }
 
@@ -690,9 +690,9 @@ static hipError_t run_f32(GemmBatch& batch, hipStream_t stream) {
   if constexpr (AT == BT) {
     long long tiles = 0;
     for (int i = 0; i < batch.n_probs; ++i) tiles += (long long)(batch.p[i].M / 64) * (batch.p[i].N / 64);
-    if (tiles >= 800) return run_f32_tiles<AT, BT, EPI, 2>(batch, stream);
+    if (tiles >= 800) return run_f32_tiles<2, AT, BT, EPI>(batch, stream);
   }
-  return run_f32_tiles<AT, BT, EPI, 1>(batch, stream);
+  return run_f32_tiles<1, AT, BT, EPI>(batch, stream);
 }
 
 // Tile shapes of the bf16 kernel: BM x BN with WM x WN waves and NS LDS stages.
