@@ -4,7 +4,8 @@
 // o [batch, seq, heads, d], log-sum-exp lse [batch, heads, seq] (natural log of
 // sum_j exp(s_ij), s = q k^T / sqrt(d)).  Keys j > i are masked.
 //
-// bf16 path (v_mfma_f32_32x32x16_bf16, fp32 softmax): flash-style tiling so the
+// bf16 path at d = 64 and 96 (d = 128 is in attention_d128.hip;
+// v_mfma_f32_32x32x16_bf16, fp32 softmax): flash-style tiling so the
 // seq x seq score matrix never reaches HBM (the method published as
 // FlashAttention, Dao et al. 2022; the gfx950 tiling below is our own).
 //   * forward: a workgroup owns 64 query rows of one (batch, head); its four
@@ -31,36 +32,9 @@
 #include <atomic>
 #include <type_traits>
 
-#include "common.h"
-#include "kernels.h"
+#include "attention.h"
 
 namespace merak {
-
-constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLn2 = 0.6931471805599453f;
-
-typedef short s16x4_t __attribute__((ext_vector_type(4)));
-typedef short s16x8_t __attribute__((ext_vector_type(8)));
-#define MERAK_LDS __attribute__((address_space(3)))
-
-// Eight accumulator values narrowed to an MFMA operand, four packed
-// conversion instructions.
-__device__ __forceinline__ bf16x8_t cvt8(const f32x16_t& a, int base) {
-  typedef float f32x8_t __attribute__((ext_vector_type(8)));
-  f32x8_t v;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) v[e] = a[base + e];
-  return __builtin_convertvector(v, bf16x8_t);
-}
-
-__device__ __forceinline__ bf16x8_t frag_kc(const bf16_t* p) { return *reinterpret_cast<const bf16x8_t*>(p); }
-
-// Sequence index of launch batch z when a launch covers several members (for
-// example the sub-micro-batches that share a stream), each of Bm consecutive
-// sequences, members mstride sequences apart.  Every tensor is addressed by
-// sequence (rows b * S + i, lse and delta rows (b * H + h) * S + i), so the
-// kernels need nothing else to work on such a group.
-__device__ __forceinline__ int seq_index(int z, int Bm, int mstride) { return (z / Bm) * mstride + z % Bm; }
 
 // Work of one workgroup: sequence, head and 64-row block.
 struct AttnSlot {
@@ -112,7 +86,6 @@ struct SwTile {
   static constexpr int NI = BYTES / 1024;   // 16-byte-per-lane wave loads per tile
   static constexpr __host__ __device__ int pos(int c, int r) {
     if constexpr (D == 64) return c ^ ((((r >> 1) & 1) << 2) | ((r >> 2) & 3));
-    else if constexpr (D == 128) return c ^ (((r & 3) << 2) | ((r >> 2) & 3));
     else return (c + ((r >> 2) & 3)) % CH;
   }
   static constexpr __host__ __device__ int chunk_at(int p, int r) {  // inverse of pos in c
@@ -230,13 +203,13 @@ __device__ __forceinline__ void step_barrier() {
 // P V product of tile t one at a time between the softmax instructions of tile
 // t.  K and V tiles sit in two-slot rings, loaded one step ahead; one barrier
 // per step.  Small tiles and 157 registers (d = 96) let three workgroups share
-// a CU.  What bounds it: on small grids the longest row block's chain (about
-// 1400 cycles a step), on large ones the vector unit (16 exponentials, 60 other
-// instructions and 12 MFMAs of 32 cycles per 32 x 32 tile).  Against 64-key
-// blocks with padded tiles and no overlap inside a wave: 4 x 1024 x 8 heads of
-// 96 18.8 -> 16.0 us, 2 x 2048 x 6 of 128 39.0 -> 29.6 us, 4 x 2048 x 25 of 96
-// 167 -> 129 us.  A third slot was 4% faster on the first of these and 6%
-// slower on the last (two workgroups per CU).
+// a CU.  What bounds it: on small grids the longest row block's chain (0.57 us a
+// step at d = 96: one pair takes 12.7 us at 1024 rows, 21.8 at 2048), on large ones
+// the vector unit (16 exponentials, 60 other instructions and 12 MFMAs of 32 cycles
+// per 32 x 32 tile).  Against 64-key blocks with padded tiles and no overlap inside
+// a wave: 4 x 1024 x 8 heads of 96 18.8 -> 16.5 us, 4 x 2048 x 25 of 96 159 -> 118.
+// A third slot was 4% faster on the first of these and 6% slower on the second (two
+// workgroups per CU).
 // ---------------------------------------------------------------------------
 template <int D>
 constexpr size_t fwd_lds_bytes() { return (size_t)8 * SwTile<D>::BYTES; }
@@ -446,17 +419,16 @@ __global__ void __launch_bounds__(256, 2) attn_fwd_bf16(int S, int H, int Bm, in
 // MFMAs run back to back: S, then dP beside the exponentials of P, then
 // dV += dO^T P beside dS = P (dP - delta), then dK += Q^T dS; each product's
 // fragments are read beside the one before it.  What bounds it: the chain of
-// steps of the first key block (about 3300 cycles each at d = 128, 1024 of them
-// MFMAs), at one (d = 128: 256 registers and 72 accumulation registers) or two
-// workgroups per CU.  Against 64-query blocks loaded after a barrier and used
-// after the next: 2 x 2048 x 6 heads of 128 67.9 -> 53.5 us, 4 x 1024 x 8 of 96
-// 34.2 -> 24.4 us.
+// steps of the first key block (0.70 us each at d = 96: one pair takes 15.5 us at
+// 1024 rows, 26.7 at 2048), with two workgroups per CU (254 registers at d = 96).
+// Against 64-query blocks loaded after a barrier and used after the next: 4 x 1024
+// x 8 heads of 96 35.1 -> 24.9 us, 4 x 2048 x 25 of 96 256 -> 206.
 // ---------------------------------------------------------------------------
 template <int D>
 constexpr size_t bwd_lds_bytes() { return (size_t)8 * SwTile<D>::BYTES + 2 * 2 * 64 * sizeof(float); }
 
 template <int D>
-__global__ void __launch_bounds__(256, (D <= 96 ? 2 : 1))
+__global__ void __launch_bounds__(256, 2)
     attn_bwd_dkdv_bf16(int S, int H, int Bm, int mstride, const bf16_t* __restrict__ qkv,
                        const bf16_t* __restrict__ dout, const float* __restrict__ lse,
                        const float* __restrict__ delta, bf16_t* __restrict__ dqkv, float scale_log2, float scale,
@@ -626,9 +598,9 @@ __global__ void __launch_bounds__(256, (D <= 96 ? 2 : 1))
 // bf16 backward: dQ (Q-parallel), the forward's layout: 64 query rows per
 // workgroup, 2 query groups x even / odd 32-key tiles, K and V tiles in two-slot
 // rings, partial dQ sums added at the end.  It also writes delta for its rows,
-// which the dK/dV kernel launched after it reads.  229 registers at d = 128 keep
-// two workgroups per CU (one before): 2 x 2048 x 6 heads of 128 51.6 -> 36.2 us;
-// 4 x 1024 x 8 of 96 25.2 -> 21.6 us.
+// which the dK/dV kernel launched after it reads.  Against 64-key blocks loaded
+// after a barrier and used after the next: 4 x 1024 x 8 heads of 96 25.3 -> 21.0 us,
+// 4 x 2048 x 25 of 96 206 -> 164.
 // ---------------------------------------------------------------------------
 template <int D>
 __global__ void __launch_bounds__(256, 2) attn_bwd_dq_bf16(int S, int H, int Bm, int mstride,
@@ -1116,7 +1088,6 @@ __global__ void __launch_bounds__(256) attn_bwd_dkdv_f32(int S, int H, int Bm, i
                                                bf16_t* __restrict__, float, float, int, AttnOrder);
 MERAK_ATTN_INST(64)
 MERAK_ATTN_INST(96)
-MERAK_ATTN_INST(128)
 #undef MERAK_ATTN_INST
 
 // Allow a kernel's dynamic LDS beyond the default limit on the current device.
@@ -1127,7 +1098,9 @@ static hipError_t allow_lds(K kern, size_t bytes, std::atomic<uint64_t>& done) {
 
 // Streamed rows of a (sequence, head) pair: 4 D bytes per token.  A chunk's
 // rows are kept to half of an XCD's 4 MB L2: without chunks, 100 pairs of 2048
-// rows at d = 128 (1 MB each) took 213 us instead of 159 in the forward.  Up to
+// rows at d = 96 (0.8 MB each) took 136 us forward, 171 for dQ and 215 for dK and dV
+// instead of 132, 164 and 206 (at d = 64, 0.5 MB each, 84, 100 and 141 instead of
+// 91, 102 and 137).  Up to
 // 512 workgroups (two per CU) are resident together, the second half of them
 // beside the first in dispatch order, so there the second half runs shortest
 // first (4 x 8 pairs of 1024 rows: 17.0 -> 16.5 us); larger grids run longest
@@ -1141,38 +1114,43 @@ static AttnOrder attn_order(int n_pairs, int S, int D) {
 }
 
 template <int D>
-static hipError_t fwd_d(int dtype, int B, int S, int H, int G, int mstride, const void* qkv, void* o, float* lse,
-                        hipStream_t st) {
-  const float scale = 1.0f / sqrtf((float)D);
-  if constexpr (D == 128)
-    if (dtype == DT_BF16) return launch_attention_fwd_d128(B, S, H, G, mstride, qkv, o, lse, st);
-  if (dtype == DT_BF16) {
+static hipError_t fwd_bf16(int B, int S, int H, int G, int mstride, const void* qkv, void* o, float* lse,
+                           hipStream_t st) {
+  if constexpr (D == 128) {
+    return launch_attention_fwd_d128(B, S, H, G, mstride, qkv, o, lse, st);
+  } else {
     constexpr size_t lds = fwd_lds_bytes<D>();
     static std::atomic<uint64_t> ok{0};
     hipError_t e = allow_lds(attn_fwd_bf16<D>, lds, ok);
     if (e != hipSuccess) return e;
     const int n_pairs = H * G * B;
     hipLaunchKernelGGL((attn_fwd_bf16<D>), dim3((unsigned)n_pairs * (S / 64)), dim3(256), lds, st, S, H, B, mstride,
-                       (const bf16_t*)qkv, (bf16_t*)o, lse, scale * kLog2e, n_pairs, attn_order(n_pairs, S, D));
-  } else {
-    constexpr size_t lds = f32_lds_bytes<D>();
-    static std::atomic<uint64_t> ok{0};
-    hipError_t e = allow_lds(attn_fwd_f32<D>, lds, ok);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((attn_fwd_f32<D>), dim3((unsigned)(H * G * B), S / 32), dim3(256), lds, st, S, H, B, mstride,
-                       (const float*)qkv, (float*)o, lse, scale);
+                       (const bf16_t*)qkv, (bf16_t*)o, lse, 1.0f / sqrtf((float)D) * kLog2e, n_pairs,
+                       attn_order(n_pairs, S, D));
+    return hipGetLastError();
   }
+}
+
+template <int D>
+static hipError_t fwd_d(int dtype, int B, int S, int H, int G, int mstride, const void* qkv, void* o, float* lse,
+                        hipStream_t st) {
+  if (dtype == DT_BF16) return fwd_bf16<D>(B, S, H, G, mstride, qkv, o, lse, st);
+  constexpr size_t lds = f32_lds_bytes<D>();
+  static std::atomic<uint64_t> ok{0};
+  hipError_t e = allow_lds(attn_fwd_f32<D>, lds, ok);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((attn_fwd_f32<D>), dim3((unsigned)(H * G * B), S / 32), dim3(256), lds, st, S, H, B, mstride,
+                     (const float*)qkv, (float*)o, lse, 1.0f / sqrtf((float)D));
   return hipGetLastError();
 }
 
 template <int D>
-static hipError_t bwd_d(int dtype, int B, int S, int H, int G, int mstride, const void* qkv, const void* o,
-                        const float* lse, const void* dout, void* dqkv, float* delta, hipStream_t st) {
-  const float scale = 1.0f / sqrtf((float)D);
-  if constexpr (D == 128)
-    if (dtype == DT_BF16)
-      return launch_attention_bwd_d128(B, S, H, G, mstride, qkv, o, lse, dout, dqkv, delta, st);
-  if (dtype == DT_BF16) {
+static hipError_t bwd_bf16(int B, int S, int H, int G, int mstride, const void* qkv, const void* o, const float* lse,
+                           const void* dout, void* dqkv, float* delta, hipStream_t st) {
+  if constexpr (D == 128) {
+    return launch_attention_bwd_d128(B, S, H, G, mstride, qkv, o, lse, dout, dqkv, delta, st);
+  } else {
+    const float scale = 1.0f / sqrtf((float)D);
     constexpr size_t lds_q = fwd_lds_bytes<D>(), lds_k = bwd_lds_bytes<D>();
     static_assert(lds_k <= 160 * 1024, "LDS budget");
     static std::atomic<uint64_t> ok_k{0}, ok_q{0};
@@ -1188,18 +1166,25 @@ static hipError_t bwd_d(int dtype, int B, int S, int H, int G, int mstride, cons
                        n_pairs, ord);
     hipLaunchKernelGGL((attn_bwd_dkdv_bf16<D>), grid, dim3(256), lds_k, st, S, H, B, mstride, (const bf16_t*)qkv,
                        (const bf16_t*)dout, lse, delta, (bf16_t*)dqkv, scale * kLog2e, scale, n_pairs, ord);
-  } else {
-    constexpr size_t lds = f32_lds_bytes<D>();
-    static std::atomic<uint64_t> ok_k{0}, ok_q{0};
-    hipError_t e = allow_lds(attn_bwd_dkdv_f32<D>, lds, ok_k);
-    if (e == hipSuccess) e = allow_lds(attn_bwd_dq_f32<D>, lds, ok_q);
-    if (e != hipSuccess) return e;
-    const dim3 grid((unsigned)(H * G * B), S / 32);
-    hipLaunchKernelGGL((attn_bwd_dq_f32<D>), grid, dim3(256), lds, st, S, H, B, mstride, (const float*)qkv,
-                       (const float*)o, (const float*)dout, lse, delta, (float*)dqkv, scale);
-    hipLaunchKernelGGL((attn_bwd_dkdv_f32<D>), grid, dim3(256), lds, st, S, H, B, mstride, (const float*)qkv,
-                       (const float*)dout, lse, delta, (float*)dqkv, scale);
+    return hipGetLastError();
   }
+}
+
+template <int D>
+static hipError_t bwd_d(int dtype, int B, int S, int H, int G, int mstride, const void* qkv, const void* o,
+                        const float* lse, const void* dout, void* dqkv, float* delta, hipStream_t st) {
+  if (dtype == DT_BF16) return bwd_bf16<D>(B, S, H, G, mstride, qkv, o, lse, dout, dqkv, delta, st);
+  const float scale = 1.0f / sqrtf((float)D);
+  constexpr size_t lds = f32_lds_bytes<D>();
+  static std::atomic<uint64_t> ok_k{0}, ok_q{0};
+  hipError_t e = allow_lds(attn_bwd_dkdv_f32<D>, lds, ok_k);
+  if (e == hipSuccess) e = allow_lds(attn_bwd_dq_f32<D>, lds, ok_q);
+  if (e != hipSuccess) return e;
+  const dim3 grid((unsigned)(H * G * B), S / 32);
+  hipLaunchKernelGGL((attn_bwd_dq_f32<D>), grid, dim3(256), lds, st, S, H, B, mstride, (const float*)qkv,
+                     (const float*)o, (const float*)dout, lse, delta, (float*)dqkv, scale);
+  hipLaunchKernelGGL((attn_bwd_dkdv_f32<D>), grid, dim3(256), lds, st, S, H, B, mstride, (const float*)qkv,
+                     (const float*)dout, lse, delta, (float*)dqkv, scale);
   return hipGetLastError();
 }
 

@@ -1,5 +1,5 @@
 // Causal attention at head dimension 128 in bf16, forward and backward: 64-row
-// padded tiles, one LDS stage of two block pairs, even and odd 64-row blocks on
+// padded tiles, one LDS stage of two blocks, even and odd 64-row blocks on
 // the two halves of a workgroup.  Same layout, grid rows and results contract as
 // the kernels for d = 64 and 96.
 //
@@ -14,60 +14,36 @@
 #include <atomic>
 #include <type_traits>
 
-#include "common.h"
-#include "kernels.h"
+#include "attention.h"
 
 namespace merak {
-namespace attn_d128 {
-
-constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLn2 = 0.6931471805599453f;
-
-typedef short s16x4_t __attribute__((ext_vector_type(4)));
-typedef short s16x8_t __attribute__((ext_vector_type(8)));
-#define MERAK_LDS __attribute__((address_space(3)))
-
-// Eight accumulator values narrowed to an MFMA operand, four packed
-// conversion instructions.
-__device__ __forceinline__ bf16x8_t cvt8(const f32x16_t& a, int base) {
-  typedef float f32x8_t __attribute__((ext_vector_type(8)));
-  f32x8_t v;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) v[e] = a[base + e];
-  return __builtin_convertvector(v, bf16x8_t);
-}
 
 // A [64 rows][D] bf16 tile in LDS with rows padded to LD elements: 16-byte
 // reads of 16 consecutive rows hit distinct banks, the transposing reads of 4
 // consecutive rows at most two-way.  LD * 2 is a multiple of 16, so the tile is
-// exactly CPR wave-instructions of 16-byte-per-lane direct loads.
-template <int D>
-struct AttnTile {
-  static constexpr int LD = D == 128 ? D + 24 : D + 8;
-  static constexpr int CPR = LD / 8;         // 16-byte chunks per padded row
-  static constexpr int DC = D / 8;           // data chunks per row
-  static constexpr int BYTES = 64 * LD * 2;  // = CPR * 1024
-};
+// exactly kChunks wave-instructions of 16-byte-per-lane direct loads.
+constexpr int D = 128, KS = D / 16, DT = D / 32;
+constexpr int LD = D + 24;
+constexpr int kChunks = LD / 8;            // 16-byte chunks per padded row
+constexpr int kTileBytes = 64 * LD * 2;    // = kChunks * 1024
 
 // One wave's plan for copying rows 0..63 of a tensor (row stride gs
 // elements) into the padded tile with loads that write LDS directly: lane i of
 // instruction q fills chunk 64 q + i (padding chunks re-read a data chunk).
 // The per-lane element offsets are computed once.
-template <int D>
 struct TileLoad {
-  using TT = AttnTile<D>;
-  uint32_t off[TT::CPR];
+  uint32_t off[kChunks];
   __device__ __forceinline__ void init(size_t gs, int lane) {
 #pragma unroll
-    for (int q = 0; q < TT::CPR; ++q) {
+    for (int q = 0; q < kChunks; ++q) {
       const int c = q * 64 + lane;
-      const int row = c / TT::CPR, ch = c % TT::CPR;
-      off[q] = (uint32_t)(row * gs) + (uint32_t)(ch < TT::DC ? ch : 0) * 8u;
+      const int row = c / kChunks, ch = c % kChunks;
+      off[q] = (uint32_t)(row * gs) + (uint32_t)(ch < D / 8 ? ch : 0) * 8u;
     }
   }
   __device__ __forceinline__ void issue(char* lds, const bf16_t* src) const {
 #pragma unroll
-    for (int q = 0; q < TT::CPR; ++q)
+    for (int q = 0; q < kChunks; ++q)
       __builtin_amdgcn_global_load_lds(src + off[q], (MERAK_LDS void*)(lds + q * 1024), 16, 0, 0);
   }
 };
@@ -78,7 +54,6 @@ __device__ __forceinline__ void wave_vec_load(char* lds, const float* src, int l
 }
 
 // 8 consecutive elements of row `row` from column `col` of a padded tile.
-template <int LD>
 __device__ __forceinline__ bf16x8_t frag_row(const char* tile, int row, int col) {
   return *reinterpret_cast<const bf16x8_t*>(tile + (row * LD + col) * 2);
 }
@@ -89,7 +64,6 @@ __device__ __forceinline__ bf16x8_t frag_row(const char* tile, int row, int col)
 // reused as the 16-deep operand.  Two transposing LDS reads: in each 16-lane
 // group, lane j fetches 4 columns of row (j / 4) and lane i receives column i of
 // the 4 rows.
-template <int LD>
 __device__ __forceinline__ bf16x8_t frag_tr(const char* tile, int kb, int col0, int lane) {
   const int row = kb + (lane >> 5) * 4 + ((lane & 15) >> 2);
   const int col = col0 + ((lane >> 4) & 1) * 16 + (lane & 3) * 4;
@@ -100,41 +74,20 @@ __device__ __forceinline__ bf16x8_t frag_tr(const char* tile, int kb, int col0, 
   return __builtin_bit_cast(bf16x8_t, v);
 }
 
-__device__ __forceinline__ bf16x8_t frag_kc(const bf16_t* p) { return *reinterpret_cast<const bf16x8_t*>(p); }
-
-// Sequence index of launch batch z when a launch covers several members (for
-// example the sub-micro-batches that share a stream), each of Bm consecutive
-// sequences, members mstride sequences apart.  Every tensor is addressed by
-// sequence (rows b * S + i, lse and delta rows (b * H + h) * S + i), so the
-// kernels need nothing else to work on such a group.
-__device__ __forceinline__ int seq_index(int z, int Bm, int mstride) { return (z / Bm) * mstride + z % Bm; }
-
-// LDS stages of the bf16 kernels (each four tiles: two 64-row blocks of two
-// tensors).  One stage keeps a workgroup small enough (53 KB at d = 96) to share
-// a CU with a GEMM workgroup of the other stream; the loads of the next block
-// pair are then issued after the current pair has been used.
-#ifndef MERAK_ATTN_STAGES
-#define MERAK_ATTN_STAGES 1
-#endif
-constexpr int kAttnStages = MERAK_ATTN_STAGES;
-static_assert(kAttnStages == 1 || kAttnStages == 2, "one or two LDS stages");
-
-template <int D>
-constexpr size_t attn_lds_bytes() { return (size_t)kAttnStages * 4 * AttnTile<D>::BYTES; }
+// One LDS stage of four tiles (two 64-row blocks of two tensors); the loads of the
+// next block pair are issued after the current pair has been used.
+constexpr size_t kLdsBytes = (size_t)4 * kTileBytes;
 
 // ---------------------------------------------------------------------------
 // bf16 forward.  A workgroup owns 64 query rows of one (batch, head); wave w
 // takes the 32 rows of group w % 2 against the even (w < 2) or odd 64-key
 // blocks, and the two halves are merged at the end (online-softmax merge).
-// Each stage holds the K and V tiles of two key blocks.
+// The stage holds the K and V tiles of two key blocks.
 // ---------------------------------------------------------------------------
-template <int D>
-__global__ void __launch_bounds__(256) attn_fwd_bf16(int S, int H, int Bm, int mstride, const bf16_t* __restrict__ qkv,
+__global__ void __launch_bounds__(256) attn_fwd_bf16_d128(int S, int H, int Bm, int mstride, const bf16_t* __restrict__ qkv,
                                                      bf16_t* __restrict__ o, float* __restrict__ lse,
                                                      float scale_log2) {
-  using TT = AttnTile<D>;
-  constexpr int LD = TT::LD, KS = D / 16, DT = D / 32, TB = TT::BYTES;
-  extern __shared__ __align__(16) char smem[];  // [stage][K blk a, K blk b, V blk a, V blk b]
+  extern __shared__ __align__(16) char smem[];  // [K blk a, K blk b, V blk a, V blk b]
 
   // Grid (heads, sequences, row blocks), row block slowest: the whole grid
   // runs longest rows first.
@@ -156,12 +109,12 @@ __global__ void __launch_bounds__(256) attn_fwd_bf16(int S, int H, int Bm, int m
 
   const int n_kb = qt + 1;  // key blocks 0..qt reach the tile's last row
   const int n_it = (n_kb + 1) / 2;
-  TileLoad<D> tl;
+  TileLoad tl;
   tl.init(rs, lane);
   const bf16_t* lsrc = (wave >> 1) ? Vp : Kp;
-  auto load_stage = [&](int it, int stage) {  // wave w: tile w of the stage
+  auto load_pair = [&](int it) {  // wave w: tile w of the stage
     const int blk = 2 * it + (wave & 1);
-    if (blk < n_kb) tl.issue(smem + (stage * 4 + wave) * TB, lsrc + (size_t)blk * 64 * rs);
+    if (blk < n_kb) tl.issue(smem + wave * kTileBytes, lsrc + (size_t)blk * 64 * rs);
   };
 
   f32x16_t oacc[DT];
@@ -179,7 +132,7 @@ __global__ void __launch_bounds__(256) attn_fwd_bf16(int S, int H, int Bm, int m
       for (int r = 0; r < 16; ++r) s[t][r] = 0.0f;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks)
-        s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_row<LD>(Kt, t * 32 + l32, ks * 16 + hf * 8), qf[ks],
+        s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_row(Kt, t * 32 + l32, ks * 16 + hf * 8), qf[ks],
                                                        s[t], 0, 0, 0);
     }
   };
@@ -234,55 +187,24 @@ __global__ void __launch_bounds__(256) attn_fwd_bf16(int S, int H, int Bm, int m
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
       for (int g = 0; g < 4; ++g)
-        oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr<LD>(Vt, g * 16, dt * 32, lane), pb[g], oacc[dt],
+        oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr(Vt, g * 16, dt * 32, lane), pb[g], oacc[dt],
                                                            0, 0, 0);
   };
 
-  if constexpr (kAttnStages == 1 && D <= 96) {
-    // One LDS stage, with K and V on separate schedules: the next block
-    // pair's K tiles are fetched while this pair's softmax and P.V run, and
-    // its V tiles while the next S = K Q^T runs.  Waves 0-1 load the K tiles
-    // and waves 2-3 the V tiles; before a barrier that publishes tiles, only
-    // the waves that loaded them wait for their own loads.  (At d = 128 the
-    // scores held across the middle barrier would cost a wave per SIMD.)
-    auto barrier = [&](bool wait_own_loads) {
-      if (wait_own_loads) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    };
-    load_stage(0, 0);
-    for (int it = 0; it < n_it; ++it) {
-      const int kb = 2 * it + kh, k0 = kb * 64;
-      const bool active = kb < n_kb && k0 <= q0 + 31;
-      f32x16_t s[2];
-      barrier(wave < 2);  // K tiles of this pair landed
-      if (active) scores(smem + kh * TB, s);
-      barrier(wave >= 2);  // every wave is done with the K tiles; V tiles landed
-      if (wave < 2 && it + 1 < n_it) load_stage(it + 1, 0);
-      if (active) softmax_pv(smem + (2 + kh) * TB, k0, s);
-      barrier(false);  // every wave is done with the V tiles
-      if (wave >= 2 && it + 1 < n_it) load_stage(it + 1, 0);
-    }
-  } else {
-    if (kAttnStages == 2) load_stage(0, 0);
-    for (int it = 0; it < n_it; ++it) {
-      const int cur = it % kAttnStages;
-      if (kAttnStages == 1) {
-        __syncthreads();  // every wave is done with the previous block pair
-        load_stage(it, 0);
-      }
-      __syncthreads();  // this block pair landed (and, with two stages, the other stage is free)
-      if (kAttnStages == 2 && it + 1 < n_it) load_stage(it + 1, (it + 1) % kAttnStages);
-      const int kb = 2 * it + kh, k0 = kb * 64;
-      if (kb >= n_kb || k0 > q0 + 31) continue;
-      f32x16_t s[2];
-      scores(smem + (cur * 4 + kh) * TB, s);
-      softmax_pv(smem + (cur * 4 + 2 + kh) * TB, k0, s);
-    }
+  for (int it = 0; it < n_it; ++it) {
+    __syncthreads();  // every wave is done with the previous block pair
+    load_pair(it);
+    __syncthreads();  // this block pair landed
+    const int kb = 2 * it + kh, k0 = kb * 64;
+    if (kb >= n_kb || k0 > q0 + 31) continue;
+    f32x16_t s[2];
+    scores(smem + kh * kTileBytes, s);
+    softmax_pv(smem + (2 + kh) * kTileBytes, k0, s);
   }
 
   // Merge the two key halves of each query group (partial m, l, O^T).
   constexpr int XS = 2 + DT * 16;
-  static_assert((size_t)128 * XS * 4 <= (size_t)kAttnStages * 4 * TB, "merge buffer fits the tiles");
+  static_assert((size_t)128 * XS * 4 <= kLdsBytes, "merge buffer fits the tiles");
   float* xch = reinterpret_cast<float*>(smem) + (size_t)(qg * 64 + lane) * XS;
   __syncthreads();
   if (kh == 1) {
@@ -319,21 +241,18 @@ __global__ void __launch_bounds__(256) attn_fwd_bf16(int S, int H, int Bm, int m
 // bf16 backward: dK, dV (KV-parallel).  A workgroup owns 64 keys of one
 // (batch, head); wave w takes the 32 keys of group w % 2 against the even
 // (w < 2) or odd 64-query blocks from the diagonal on, and the two partial sums
-// are added at the end.  Each stage holds the Q and dO tiles (and lse, delta)
+// are added at the end.  The stage holds the Q and dO tiles (and lse, delta)
 // of two query blocks.  P is rebuilt from lse.
 // ---------------------------------------------------------------------------
-template <int D>
-__global__ void __launch_bounds__(256) attn_bwd_dkdv_bf16(int S, int H, int Bm, int mstride,
+__global__ void __launch_bounds__(256) attn_bwd_dkdv_bf16_d128(int S, int H, int Bm, int mstride,
                                                           const bf16_t* __restrict__ qkv,
                                                           const bf16_t* __restrict__ dout,
                                                           const float* __restrict__ lse,
                                                           const float* __restrict__ delta,
                                                           bf16_t* __restrict__ dqkv, float scale_log2,
                                                           float scale) {
-  using TT = AttnTile<D>;
-  constexpr int LD = TT::LD, KS = D / 16, DT = D / 32, TB = TT::BYTES;
-  extern __shared__ __align__(16) char smem[];  // [stage][Q a, Q b, dO a, dO b], then lse/delta
-  float* vecs = reinterpret_cast<float*>(smem + kAttnStages * 4 * TB);  // [stage][lse a|b, delta a|b]
+  extern __shared__ __align__(16) char smem[];  // [Q a, Q b, dO a, dO b], then lse/delta
+  float* vecs = reinterpret_cast<float*>(smem + kLdsBytes);  // [lse a|b, delta a|b]
 
   // Grid (heads, sequences, key blocks), key block slowest: early keys see the
   // most queries, so the whole grid runs longest columns first.
@@ -369,34 +288,29 @@ __global__ void __launch_bounds__(256) attn_bwd_dkdv_bf16(int S, int H, int Bm, 
   const int n_it = (n_qb + 1) / 2;
   const bool is_do = (wave >> 1) != 0;
   const size_t lgs = is_do ? ors : rs;
-  TileLoad<D> tl;
+  TileLoad tl;
   tl.init(lgs, lane);
   const bf16_t* lsrc = is_do ? dOp : Qp;
   const float* vsrc = is_do ? del_p : lse_p;
-  auto load_stage = [&](int it, int stage) {
+  auto load_pair = [&](int it) {
     const int blk = kt + 2 * it + (wave & 1);
     if (2 * it + (wave & 1) < n_qb) {
-      tl.issue(smem + (stage * 4 + wave) * TB, lsrc + (size_t)blk * 64 * lgs);
-      float* v = vecs + stage * 256 + (wave & 1) * 64 + (is_do ? 128 : 0);
+      tl.issue(smem + wave * kTileBytes, lsrc + (size_t)blk * 64 * lgs);
+      float* v = vecs + (wave & 1) * 64 + (is_do ? 128 : 0);
       if (is_do) wave_vec_load(reinterpret_cast<char*>(v), vsrc + (size_t)blk * 64, lane);
       else v[lane] = vsrc[(size_t)blk * 64 + lane] * kLog2e;  // lse staged in log2 units
     }
   };
 
-  if (kAttnStages == 2) load_stage(0, 0);
   for (int it = 0; it < n_it; ++it) {
-    const int cur = it % kAttnStages;
-    if (kAttnStages == 1) {
-      __syncthreads();
-      load_stage(it, 0);
-    }
     __syncthreads();
-    if (kAttnStages == 2 && it + 1 < n_it) load_stage(it + 1, (it + 1) % kAttnStages);
+    load_pair(it);
+    __syncthreads();
     const int qb = kt + 2 * it + qh, qs = qb * 64;
     if (2 * it + qh >= n_qb || qs + 63 < kw0) continue;
-    const char* Qt = smem + (cur * 4 + qh) * TB;
-    const char* dOt = smem + (cur * 4 + 2 + qh) * TB;
-    const float* lse_s = vecs + cur * 256 + qh * 64;
+    const char* Qt = smem + qh * kTileBytes;
+    const char* dOt = smem + (2 + qh) * kTileBytes;
+    const float* lse_s = vecs + qh * 64;
     const float* del_s = lse_s + 128;
 
     // The two 32-query halves of the block one after the other (smaller live
@@ -414,9 +328,9 @@ __global__ void __launch_bounds__(256) attn_bwd_dkdv_bf16(int S, int H, int Bm, 
       for (int r = 0; r < 16; ++r) p[r] = dp[r] = 0.0f;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
-        p = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_row<LD>(Qt, t * 32 + l32, ks * 16 + hf * 8), kf[ks], p, 0,
+        p = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_row(Qt, t * 32 + l32, ks * 16 + hf * 8), kf[ks], p, 0,
                                                     0, 0);
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_row<LD>(dOt, t * 32 + l32, ks * 16 + hf * 8), vf[ks], dp,
+        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_row(dOt, t * 32 + l32, ks * 16 + hf * 8), vf[ks], dp,
                                                      0, 0, 0);
       }
       // p[r]: query qs + t*32 + (r/4)*8 + 4*hf + r%4, key `key`.
@@ -437,9 +351,9 @@ __global__ void __launch_bounds__(256) attn_bwd_dkdv_bf16(int S, int H, int Bm, 
 #pragma unroll
         for (int gg = 0; gg < 2; ++gg) {
           const int g = 2 * t + gg;
-          dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr<LD>(dOt, g * 16, dt * 32, lane), pb[gg], dv[dt],
+          dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr(dOt, g * 16, dt * 32, lane), pb[gg], dv[dt],
                                                            0, 0, 0);
-          dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr<LD>(Qt, g * 16, dt * 32, lane), sb[gg], dk[dt],
+          dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr(Qt, g * 16, dt * 32, lane), sb[gg], dk[dt],
                                                            0, 0, 0);
         }
     }
@@ -447,7 +361,7 @@ __global__ void __launch_bounds__(256) attn_bwd_dkdv_bf16(int S, int H, int Bm, 
 
   // Add the two query halves.
   constexpr int XS = 2 * DT * 16;
-  static_assert((size_t)128 * XS * 4 <= (size_t)kAttnStages * 4 * TB, "merge buffer fits the tiles");
+  static_assert((size_t)128 * XS * 4 <= kLdsBytes, "merge buffer fits the tiles");
   float* xch = reinterpret_cast<float*>(smem) + (size_t)(kg * 64 + lane) * XS;
   __syncthreads();
   if (qh == 1) {
@@ -480,20 +394,17 @@ __global__ void __launch_bounds__(256) attn_bwd_dkdv_bf16(int S, int H, int Bm, 
 
 // ---------------------------------------------------------------------------
 // bf16 backward: dQ (Q-parallel), the forward's layout: 64 query rows per
-// workgroup, 2 query groups x 2 key halves, K and V tiles of two key blocks per
+// workgroup, 2 query groups x 2 key halves, K and V tiles of two key blocks in the
 // stage, partial dQ sums added at the end.  It also writes delta for its rows,
 // which the dK/dV kernel launched after it reads.
 // ---------------------------------------------------------------------------
-template <int D>
-__global__ void __launch_bounds__(256) attn_bwd_dq_bf16(int S, int H, int Bm, int mstride,
+__global__ void __launch_bounds__(256) attn_bwd_dq_bf16_d128(int S, int H, int Bm, int mstride,
                                                         const bf16_t* __restrict__ qkv,
                                                         const bf16_t* __restrict__ o,
                                                         const bf16_t* __restrict__ dout,
                                                         const float* __restrict__ lse,
                                                         float* __restrict__ delta,
                                                         bf16_t* __restrict__ dqkv, float scale_log2, float scale) {
-  using TT = AttnTile<D>;
-  constexpr int LD = TT::LD, KS = D / 16, DT = D / 32, TB = TT::BYTES;
   extern __shared__ __align__(16) char smem[];
 
   const int b = seq_index(blockIdx.y, Bm, mstride), hh = blockIdx.x;  // grid as in the forward
@@ -543,27 +454,22 @@ __global__ void __launch_bounds__(256) attn_bwd_dq_bf16(int S, int H, int Bm, in
 
   const int n_kb = qt + 1;
   const int n_it = (n_kb + 1) / 2;
-  TileLoad<D> tl;
+  TileLoad tl;
   tl.init(rs, lane);
   const bf16_t* lsrc = (wave >> 1) ? Vp : Kp;
-  auto load_stage = [&](int it, int stage) {
+  auto load_pair = [&](int it) {
     const int blk = 2 * it + (wave & 1);
-    if (blk < n_kb) tl.issue(smem + (stage * 4 + wave) * TB, lsrc + (size_t)blk * 64 * rs);
+    if (blk < n_kb) tl.issue(smem + wave * kTileBytes, lsrc + (size_t)blk * 64 * rs);
   };
 
-  if (kAttnStages == 2) load_stage(0, 0);
   for (int it = 0; it < n_it; ++it) {
-    const int cur = it % kAttnStages;
-    if (kAttnStages == 1) {
-      __syncthreads();
-      load_stage(it, 0);
-    }
     __syncthreads();
-    if (kAttnStages == 2 && it + 1 < n_it) load_stage(it + 1, (it + 1) % kAttnStages);
+    load_pair(it);
+    __syncthreads();
     const int kb = 2 * it + kh, k0 = kb * 64;
     if (kb >= n_kb || k0 > q0 + 31) continue;
-    const char* Kt = smem + (cur * 4 + kh) * TB;
-    const char* Vt = smem + (cur * 4 + 2 + kh) * TB;
+    const char* Kt = smem + kh * kTileBytes;
+    const char* Vt = smem + (2 + kh) * kTileBytes;
     f32x16_t p[2], dp[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -571,9 +477,9 @@ __global__ void __launch_bounds__(256) attn_bwd_dq_bf16(int S, int H, int Bm, in
       for (int r = 0; r < 16; ++r) p[t][r] = dp[t][r] = 0.0f;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
-        p[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_row<LD>(Kt, t * 32 + l32, ks * 16 + hf * 8), qf[ks], p[t],
+        p[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_row(Kt, t * 32 + l32, ks * 16 + hf * 8), qf[ks], p[t],
                                                        0, 0, 0);
-        dp[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_row<LD>(Vt, t * 32 + l32, ks * 16 + hf * 8), of[ks],
+        dp[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_row(Vt, t * 32 + l32, ks * 16 + hf * 8), of[ks],
                                                         dp[t], 0, 0, 0);
       }
     }
@@ -600,11 +506,11 @@ __global__ void __launch_bounds__(256) attn_bwd_dq_bf16(int S, int H, int Bm, in
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
       for (int g = 0; g < 4; ++g)
-        dq[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr<LD>(Kt, g * 16, dt * 32, lane), sb[g], dq[dt], 0, 0, 0);
+        dq[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr(Kt, g * 16, dt * 32, lane), sb[g], dq[dt], 0, 0, 0);
   }
 
   constexpr int XS = DT * 16;
-  static_assert((size_t)128 * XS * 4 <= (size_t)kAttnStages * 4 * TB, "merge buffer fits the tiles");
+  static_assert((size_t)128 * XS * 4 <= kLdsBytes, "merge buffer fits the tiles");
   float* xch = reinterpret_cast<float*>(smem) + (size_t)(qg * 64 + lane) * XS;
   __syncthreads();
   if (kh == 1) {
@@ -627,51 +533,31 @@ __global__ void __launch_bounds__(256) attn_bwd_dq_bf16(int S, int H, int Bm, in
     }
 }
 
-// The host pass then always emits their launch stubs.
-#define MERAK_ATTN_INST(D)                                                                                        \
-  template __global__ void attn_fwd_bf16<D>(int, int, int, int, const bf16_t* __restrict__, bf16_t* __restrict__, \
-                                            float* __restrict__, float);                                         \
-  template __global__ void attn_bwd_dkdv_bf16<D>(int, int, int, int, const bf16_t* __restrict__,                 \
-                                                 const bf16_t* __restrict__, const float* __restrict__,          \
-                                                 const float* __restrict__, bf16_t* __restrict__, float, float); \
-  template __global__ void attn_bwd_dq_bf16<D>(int, int, int, int, const bf16_t* __restrict__,                   \
-                                               const bf16_t* __restrict__, const bf16_t* __restrict__,           \
-                                               const float* __restrict__, float* __restrict__,                   \
-                                               bf16_t* __restrict__, float, float);
-MERAK_ATTN_INST(128)
-#undef MERAK_ATTN_INST
-}  // namespace attn_d128
-using namespace attn_d128;
-
 hipError_t launch_attention_fwd_d128(int B, int S, int H, int G, int mstride, const void* qkv, void* o, float* lse,
                                      hipStream_t st) {
-  constexpr int D = 128;
   const float scale = 1.0f / sqrtf((float)D);
-  constexpr size_t lds = attn_lds_bytes<D>();
   static std::atomic<uint64_t> ok{0};
-  hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(attn_fwd_bf16<D>), lds, ok);
+  hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(attn_fwd_bf16_d128), kLdsBytes, ok);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((attn_fwd_bf16<D>), dim3(H, G * B, S / 64), dim3(256), lds, st, S, H, B, mstride,
+  hipLaunchKernelGGL((attn_fwd_bf16_d128), dim3(H, G * B, S / 64), dim3(256), kLdsBytes, st, S, H, B, mstride,
                      (const bf16_t*)qkv, (bf16_t*)o, lse, scale * kLog2e);
   return hipGetLastError();
 }
 
 hipError_t launch_attention_bwd_d128(int B, int S, int H, int G, int mstride, const void* qkv, const void* o,
                                      const float* lse, const void* dout, void* dqkv, float* delta, hipStream_t st) {
-  constexpr int D = 128;
   const float scale = 1.0f / sqrtf((float)D);
-  constexpr size_t lds_q = attn_lds_bytes<D>();
-  constexpr size_t lds_k = attn_lds_bytes<D>() + kAttnStages * 256 * sizeof(float);
+  constexpr size_t lds_q = kLdsBytes, lds_k = kLdsBytes + 256 * sizeof(float);
   static_assert(lds_k <= 160 * 1024, "LDS budget");
   static std::atomic<uint64_t> ok_k{0}, ok_q{0};
-  hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(attn_bwd_dkdv_bf16<D>), lds_k, ok_k);
-  if (e == hipSuccess) e = allow_dynamic_lds(reinterpret_cast<const void*>(attn_bwd_dq_bf16<D>), lds_q, ok_q);
+  hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(attn_bwd_dkdv_bf16_d128), lds_k, ok_k);
+  if (e == hipSuccess) e = allow_dynamic_lds(reinterpret_cast<const void*>(attn_bwd_dq_bf16_d128), lds_q, ok_q);
   if (e != hipSuccess) return e;
   // dQ first: it also forms delta, which dK/dV reads.
   const dim3 grid(H, G * B, S / 64);
-  hipLaunchKernelGGL((attn_bwd_dq_bf16<D>), grid, dim3(256), lds_q, st, S, H, B, mstride, (const bf16_t*)qkv,
+  hipLaunchKernelGGL((attn_bwd_dq_bf16_d128), grid, dim3(256), lds_q, st, S, H, B, mstride, (const bf16_t*)qkv,
                      (const bf16_t*)o, (const bf16_t*)dout, lse, delta, (bf16_t*)dqkv, scale * kLog2e, scale);
-  hipLaunchKernelGGL((attn_bwd_dkdv_bf16<D>), grid, dim3(256), lds_k, st, S, H, B, mstride, (const bf16_t*)qkv,
+  hipLaunchKernelGGL((attn_bwd_dkdv_bf16_d128), grid, dim3(256), lds_k, st, S, H, B, mstride, (const bf16_t*)qkv,
                      (const bf16_t*)dout, lse, delta, (bf16_t*)dqkv, scale * kLog2e, scale);
   return hipGetLastError();
 }

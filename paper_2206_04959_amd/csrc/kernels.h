@@ -118,15 +118,16 @@ hipError_t noalloc_scratch(float** out);
 // cover `members` groups of `batch` sequences each, member m starting
 // m * member_stride sequences after the pointers given (so the sub-micro-
 // batches that share a stream form one grid); member_stride >= batch.
-// bf16 attention at d = 128 (batch, seq, heads, members, member stride).
-hipError_t launch_attention_fwd_d128(int B, int S, int H, int G, int mstride, const void* qkv, void* o, float* lse,
-                                     hipStream_t st);
-hipError_t launch_attention_bwd_d128(int B, int S, int H, int G, int mstride, const void* qkv, const void* o,
-                                     const float* lse, const void* dout, void* dqkv, float* delta, hipStream_t st);
 hipError_t launch_attention_fwd(int dtype, int batch, int seq, int heads, int d, const void* qkv, void* o,
                                 float* lse, hipStream_t stream, int members = 1, int member_stride = 0);
 hipError_t launch_attention_bwd(int dtype, int batch, int seq, int heads, int d, const void* qkv,
                                 const void* o, const float* lse, const void* dout, void* dqkv,
                                 float* delta, hipStream_t stream, int members = 1, int member_stride = 0);
+
+// The launches above for bf16 at d = 128 (batch, seq, heads, members, member stride).
+hipError_t launch_attention_fwd_d128(int B, int S, int H, int G, int mstride, const void* qkv, void* o, float* lse,
+                                     hipStream_t st);
+hipError_t launch_attention_bwd_d128(int B, int S, int H, int G, int mstride, const void* qkv, const void* o,
+                                     const float* lse, const void* dout, void* dqkv, float* delta, hipStream_t st);
 
 }  // namespace merak
