@@ -123,12 +123,17 @@ def test_gemm_fp32_large_tiles(epi, a_t, b_t):
         assert rel_err(out[0][0][M - 64:].cpu().numpy(), ref) < 1e-5
 
 
-# (M, N, K) for which the choice for a lone launch is 64x128 (or 128x128 where A
-# is read transposed), 128x128, 192x128, 128x192 and 256x128 tiles, each with
-# ragged last tiles and more K stages than the ring holds; and one K stage.
+# The tile that a lone launch of each (M, N, K) takes (64x128 tiles need A with K
+# contiguous; where it is read transposed another is taken), each with ragged last tiles and
+# more K stages than the ring holds; and the fewest stages that the two small shapes
+# are chosen at, one and two.  test_tile_choice.py holds the choice to this table.
+LONE_TILES = {(960, 1088, 320): "64x128", (1984, 1600, 320): "128x128", (3008, 1984, 576): "192x128",
+              (1984, 3008, 576): "128x192", (3840, 1984, 576): "256x128", (960, 1088, 64): "128x128",
+              (1984, 1600, 64): "128x128", (320, 448, 128): "64x128"}
+
+
 @pytest.mark.parametrize("a_t,b_t", [(0, 0), (0, 1), (1, 1), (1, 0)])
-@pytest.mark.parametrize("mnk", [(960, 1088, 320), (1984, 1600, 320), (3008, 1984, 576), (1984, 3008, 576),
-                                 (3840, 1984, 576), (960, 1088, 64), (1984, 1600, 64)])
+@pytest.mark.parametrize("mnk", LONE_TILES)
 def test_gemm_lone_launch_tiles(mnk, a_t, b_t):
     """fp32 output, so the tolerance is that of fp32 sums of up to 576 products
     of bf16 values (2e-5 of the largest, as for every tile shape below)."""
@@ -144,8 +149,10 @@ def test_gemm_lone_launch_tiles(mnk, a_t, b_t):
     assert rel_err(c32.cpu().numpy(), ref) < 2e-5
 
 
-# bf16: the automatic tile choice and each tile the stage's choice can make
-# (256x256, 256x128 and 128x192 tiles, 256x192); fp32 has one kernel.
+# bf16: the automatic tile choice, the forced shapes the stage's choice can make
+# (7, 8 and 10: 256x256, 256x128 and 256x192) and 9 (128x192 on four waves, by
+# override only); fp32 has one kernel at this size.  The shapes that only the choice
+# itself reaches are in the test after it.
 EPI_CASES = [("bf16", 0), ("bf16", 7), ("bf16", 8), ("bf16", 9), ("bf16", 10), ("fp32", 0)]
 
 
@@ -160,8 +167,18 @@ def test_gemm_epilogues(dtype, tile):
         B.gemm_tile_override(prev)
 
 
-def _gemm_epilogues(torch, dtype):
-    M, N, K = 320, 448, 192
+@pytest.mark.parametrize("mnk", [k for k in LONE_TILES if k[2] > 128])
+def test_gemm_epilogues_lone_launch(mnk):
+    """Every fused epilogue on each tile that only a lone launch's choice reaches
+    (the stage's narrow launches take the 128x128 one too), GeLU' also with the
+    weight read in place, as the input gradient does."""
+    torch = need_gpu()
+    print(f"[gemm epilogues] lone launch {mnk}: {LONE_TILES[mnk]}", flush=True)
+    _gemm_epilogues(torch, "bf16", mnk)
+
+
+def _gemm_epilogues(torch, dtype, mnk=(320, 448, 192)):
+    M, N, K = mnk
     a_p, a = _rand((M, K), dtype, 3)
     w_p, w = _rand((N, K), dtype, 4, std=0.1)
     bias_p, bias = _rand((N,), dtype, 5, std=0.5)
@@ -189,6 +206,9 @@ def _gemm_epilogues(torch, dtype):
     u_p, u = _rand((M, N), dtype, 7, std=2.0)
     U = _dev(u_p)
     B.gemm(A, W, c, M, N, K, epilogue=B.EPI_GELU_BWD, aux=U)
+    torch.cuda.synchronize()
+    assert rel_err(B.to_host_f64(c), acc * oracle.gelu_grad(u)) < tol
+    B.gemm(A, W.t().contiguous(), c, M, N, K, b_trans=True, epilogue=B.EPI_GELU_BWD, aux=U)
     torch.cuda.synchronize()
     assert rel_err(B.to_host_f64(c), acc * oracle.gelu_grad(u)) < tol
 
