@@ -387,17 +387,20 @@ typedef enum {
  *             1: B[k,n] at b[k*ldb + n].
  * M, N, K must be positive multiples of 64 and lda, ldb multiples of 8, and in
  * MERAK_BF16 each operand, counted with 256 rows of edge-tile padding past M
- * (or N), must span fewer than 2^31 bytes (else MERAK_ERR_SHAPE).  C, resid and aux are [M, N] row-major (ld = N); bias is
- * [N].  Elements are of `dtype` except C for MERAK_EPI_F32 (always fp32). */
+ * (or N), must span fewer than 2^31 bytes (else MERAK_ERR_SHAPE).  C, resid and
+ * aux are [M, N] row-major (ld = N); bias is [N].  Elements are of `dtype` except
+ * C for MERAK_EPI_F32 (always fp32).  The bf16 tile shape is chosen for a call that
+ * has the chip to itself; results do not depend on it. */
 int merak_gemm(int dtype, int a_trans, int b_trans, int epilogue, int M, int N, int K,
                const void* a, int lda, const void* b, int ldb, void* c, const void* bias,
                const void* resid, void* aux, int accumulate, void* stream);
 
 /* Tile-shape override of the bf16 GEMM kernel, for tests and tuning:
- * 0 restores the built-in choice, 1..10 force one shape (256x256/4 waves/2
- * stages, 256x128/4/3, 128x256/4/3, 128x128/4/2, 128x128/4/3, 128x128/4/4,
- * 256x256/8/2, 256x128/8/3, 128x192/4/2, 256x192/8/2).  Process-wide; returns the previous value, or -1
- * for an out-of-range cfg (nothing changed).  Host-only, not thread-safe. */
+ * 0 restores the built-in choice, which also has shapes of its own; 1..10 force
+ * one (256x256/4 waves/2 stages, 256x128/4/3, 128x256/4/3, 128x128/4/2,
+ * 128x128/4/3, 128x128/4/4, 256x256/8/2, 256x128/8/3, 128x192/4/2, 256x192/8/2).
+ * Process-wide; returns the previous value, or -1 for an out-of-range cfg (nothing
+ * changed).  Host-only, not thread-safe. */
 int merak_gemm_tile_override(int cfg);
 
 /* LayerNorm forward over `rows` rows of width h (h % 8 == 0, h <= 8192):

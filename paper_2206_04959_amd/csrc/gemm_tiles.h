@@ -74,6 +74,11 @@ inline int choose_tile_shared(const GemmBatch& b, bool b_t) {
 // -> after): 2048 x 1600 x 1600 26.4 -> 17.3, 4096 x 768 x 3072 37.4 -> 24.7,
 // 1024 x 1024 x 1280 18.3 -> 10.4, 1920 x 3840 x 4096 (weight gradient) 73 ->
 // 65.6, 4096 x 4096 x 4096 144 -> 110; 4096 x 3072 x 3072 stays 68.4.
+// Two calls at once, one per stream, take between 0.6 and 1.1 times what they took
+// with the rule above and 128 x 192 tiles of four waves as its last shape (us a
+// pair): 1024 x 1024 x 1024 18.2 -> 10.3, 2048 x 6400 x 1600 87 -> 83, 2048 x 1920 x
+// 3840 with 2048 x 1600 x 1600 54 -> 47; but 8192 x 3072 x 3072 237 -> 248, 2048 x 1920
+// x 3840 60 -> 63 and 1920 x 3840 x 4096 (weight gradient) 112 -> 124.
 inline int choose_tile_alone(const GemmBatch& b, bool a_t) {
   static const struct {
     int bm, bn, cfg;

@@ -263,15 +263,19 @@ def test_backward_calls_of_several_handles(pairs):
     for r in runs:
         r.grads.fill_(float("nan"))
     torch.cuda.synchronize()
+    for r, p in zip(runs, pairs):  # each on its pair, then all on another, ordered by events only
+        _step(r, runs[p].streams)
+    for p in set(pairs):
+        runs[2].streams[0].wait_stream(runs[p].streams[0])
     for r in runs:
         _step(r, runs[2].streams)
     torch.cuda.synchronize()
     assert all(_same(r.raw(), a) for r, a in zip(runs, alone))
     for i in (1, 2):
-        runs[i - 1].stage.close()
         runs[i].grads.fill_(float("nan"))
         torch.cuda.synchronize()
         _step(runs[i], runs[2].streams)
+        runs[i - 1].stage.close()  # its own work is done; the step before is on its way
         torch.cuda.synchronize()
         assert _same(runs[i].raw(), alone[i])
 
