@@ -84,9 +84,9 @@ constexpr size_t kLdsBytes = (size_t)4 * kTileBytes;
 // blocks, and the two halves are merged at the end (online-softmax merge).
 // The stage holds the K and V tiles of two key blocks.
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) attn_fwd_bf16_d128(int S, int H, int Bm, int mstride, const bf16_t* __restrict__ qkv,
-                                                     bf16_t* __restrict__ o, float* __restrict__ lse,
-                                                     float scale_log2) {
+__global__ void __launch_bounds__(256) attn_fwd_bf16_d128(int S, int H, int Bm, int mstride,
+                                                          const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o,
+                                                          float* __restrict__ lse, float scale_log2) {
   extern __shared__ __align__(16) char smem[];  // [K blk a, K blk b, V blk a, V blk b]
 
   // Grid (heads, sequences, row blocks), row block slowest: the whole grid
@@ -244,13 +244,10 @@ __global__ void __launch_bounds__(256) attn_fwd_bf16_d128(int S, int H, int Bm, 
 // are added at the end.  The stage holds the Q and dO tiles (and lse, delta)
 // of two query blocks.  P is rebuilt from lse.
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) attn_bwd_dkdv_bf16_d128(int S, int H, int Bm, int mstride,
-                                                          const bf16_t* __restrict__ qkv,
-                                                          const bf16_t* __restrict__ dout,
-                                                          const float* __restrict__ lse,
-                                                          const float* __restrict__ delta,
-                                                          bf16_t* __restrict__ dqkv, float scale_log2,
-                                                          float scale) {
+__global__ void __launch_bounds__(256)
+    attn_bwd_dkdv_bf16_d128(int S, int H, int Bm, int mstride, const bf16_t* __restrict__ qkv,
+                            const bf16_t* __restrict__ dout, const float* __restrict__ lse,
+                            const float* __restrict__ delta, bf16_t* __restrict__ dqkv, float scale_log2, float scale) {
   extern __shared__ __align__(16) char smem[];  // [Q a, Q b, dO a, dO b], then lse/delta
   float* vecs = reinterpret_cast<float*>(smem + kLdsBytes);  // [lse a|b, delta a|b]
 
@@ -398,13 +395,11 @@ __global__ void __launch_bounds__(256) attn_bwd_dkdv_bf16_d128(int S, int H, int
 // stage, partial dQ sums added at the end.  It also writes delta for its rows,
 // which the dK/dV kernel launched after it reads.
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) attn_bwd_dq_bf16_d128(int S, int H, int Bm, int mstride,
-                                                        const bf16_t* __restrict__ qkv,
-                                                        const bf16_t* __restrict__ o,
-                                                        const bf16_t* __restrict__ dout,
-                                                        const float* __restrict__ lse,
-                                                        float* __restrict__ delta,
-                                                        bf16_t* __restrict__ dqkv, float scale_log2, float scale) {
+__global__ void __launch_bounds__(256)
+    attn_bwd_dq_bf16_d128(int S, int H, int Bm, int mstride, const bf16_t* __restrict__ qkv,
+                          const bf16_t* __restrict__ o, const bf16_t* __restrict__ dout,
+                          const float* __restrict__ lse, float* __restrict__ delta, bf16_t* __restrict__ dqkv,
+                          float scale_log2, float scale) {
   extern __shared__ __align__(16) char smem[];
 
   const int b = seq_index(blockIdx.y, Bm, mstride), hh = blockIdx.x;  // grid as in the forward
