@@ -225,8 +225,10 @@ struct merak_stage {
   char* ws;
   char* rc;
   int dev;  // the device current at creation
-  std::shared_ptr<AuxStream> own, spare;          // for weight gradients (AuxStream below)
-  std::shared_ptr<AuxStream> pairs[kAuxPairs];    // streams of the pairs it has been used on; under g_mu, as spare
+  // streams for weight gradients (AuxStream below); under g_mu
+  std::shared_ptr<AuxStream> own;               // brought by this handle, until it is given to a pair
+  AuxStream* given;                             // the one that was (kept in pairs)
+  std::shared_ptr<AuxStream> pairs[kAuxPairs];  // streams of the pairs it has been used on
   hipEvent_t ev_fork, ev_s1, ev_j0, ev_j1, ev_aux, ev_dw[2];
   hipEvent_t ev_rc[kMaxBlocks][2];  // recompute of block l done on its two streams
   int state;  // 0 idle, 1 forward pending, 2 recomputed
@@ -257,36 +259,33 @@ std::map<void*, merak_stage*> g_rc_owner;  // recompute area -> handle that last
 //
 // Sharing adds no wait.  Calls on one pair wait for each other in any case (a
 // backward call ends with stream0 waiting for the weight gradients, and the next
-// one's start with what stream0 has reached).  Calls on different pairs, where one
-// may be held back by a receive that another's work has to answer, never meet on a
-// stream, also where one handle has been used on both.  (A caller's stream is
-// destroyed after its work: a new one at its address finds the pair's stream idle.)
+// one's start with what stream0 has reached); under graph capture they are captured
+// together.  Calls on different pairs, where one may be held back by a receive that
+// another's work has to answer, never meet on a stream, also where one handle has
+// been used on both.  (A caller's stream is destroyed after its work: a new one at
+// its address finds the pair's stream idle.)
 //
-// A handle brings two streams: one that only its own calls use, and one that it
-// gives to the first pair it meets that no handle has served yet.  A pair's stream
-// lives until the last handle that has used it is destroyed, after its work.  A
-// call takes its handle's own stream where the pair's would not be the pair's
-// alone (under graph capture, while another host thread's call enqueues to it, and
-// for the per-thread stream, which is another stream in each thread) and where the
-// handle keeps kAuxPairs streams already.
+// A handle brings one stream (a second one, even unused, shifts the caller's streams
+// to other hardware queues: the 8.3B-shaped step of one handle took 11.3 ms instead
+// of 10.0) and gives it to the first pair it meets that no handle has served yet; it
+// takes it along to another pair while no other handle has used it.  A pair's stream
+// lives until the last handle that has used it is destroyed, after its work.  A call
+// takes its handle's own stream, if that serves no pair yet, and else stream1, where
+// the pair's would not be the pair's alone (while another host thread's call
+// enqueues to it, and for the per-thread stream, which is another stream in each
+// thread), and where there is none: on stream1 the weight gradients wait for nothing
+// new either, but run between the chains instead of beside them.
 struct AuxStream {
   hipStream_t st = nullptr;
-  int dev = 0;
   hipStream_t s0 = nullptr, s1 = nullptr;  // the pair served
-  bool busy = false;                       // a call is enqueueing to it; under g_mu
+  int dev = 0;
+  bool busy = false;  // a call is enqueueing to it; under g_mu
   ~AuxStream() {
     if (st) (void)hipStreamDestroy(st);
   }
 };
 using AuxRef = std::shared_ptr<AuxStream>;
 std::vector<AuxRef> g_pairs;  // streams that serve a pair; under g_mu
-
-bool capturing(hipStream_t st) {
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
-  (void)hipGetLastError();  // a failed query is not the next launch's error
-  return true;
-}
 
 hipError_t make_aux(int dev, AuxRef* out) {
   try {
@@ -298,30 +297,37 @@ hipError_t make_aux(int dev, AuxRef* out) {
   return hipStreamCreateWithFlags(&(*out)->st, hipStreamNonBlocking);
 }
 
-// The stream that serves the pair, kept by S from now on; null if there is none
-// and S has none to give, or if S keeps as many as it may.
+// The stream that serves the pair, kept by S from now on; null if there is none and
+// S has none to give or to take along, or if S keeps as many as it may.  Under g_mu.
 AuxStream* pair_stream(merak_stage* S, hipStream_t s0, hipStream_t s1) {
   auto serves = [&](const AuxRef& a) { return a && a->dev == S->dev && a->s0 == s0 && a->s1 == s1; };
-  AuxRef* slot = nullptr;
+  AuxRef *slot = nullptr, *given = nullptr;
   for (AuxRef& a : S->pairs) {
     if (serves(a)) return a.get();
     if (!a && !slot) slot = &a;
+    if (a && a.get() == S->given) given = &a;
   }
-  if (!slot) return nullptr;
   const auto it = std::find_if(g_pairs.begin(), g_pairs.end(), serves);
   if (it != g_pairs.end()) {
+    if (!slot) return nullptr;
     *slot = *it;
-  } else if (S->spare) {
+    return slot->get();
+  }
+  if (S->own) {
+    if (!slot) return nullptr;
     try {
-      g_pairs.push_back(S->spare);
+      g_pairs.push_back(S->own);
     } catch (const std::bad_alloc&) {
       return nullptr;
     }
-    S->spare->s0 = s0;
-    S->spare->s1 = s1;
-    *slot = std::move(S->spare);
+    S->given = S->own.get();
+    *slot = std::move(S->own);
+  } else if (!given || given->use_count() > 2) {  // S's and g_pairs': no other handle has used it
+    return nullptr;
   }
-  return slot->get();
+  S->given->s0 = s0;
+  S->given->s1 = s1;
+  return S->given;
 }
 
 // S keeps its pairs' streams no longer.  They are moved to `out`, to be let go of
@@ -338,26 +344,28 @@ void leave_pairs(merak_stage* S, AuxRef (&out)[kAuxPairs]) {
 // The stream of one backward call, for as long as it enqueues.
 class AuxLoan {
  public:
-  AuxLoan(merak_stage* S, hipStream_t s0, hipStream_t s1) : aux_(S->own.get()) {
-    int dev = -1;
-    if (s0 == hipStreamPerThread || s1 == hipStreamPerThread || capturing(s0)) return;
-    if (hipGetDevice(&dev) != hipSuccess || dev != S->dev) return;  // the null stream is another one there
+  AuxLoan(merak_stage* S, hipStream_t s0, hipStream_t s1) : st_(s1) {
+    int dev = -1;  // the null stream is another one on another device
+    const bool shared = s0 != hipStreamPerThread && s1 != hipStreamPerThread && hipGetDevice(&dev) == hipSuccess &&
+                        dev == S->dev;
     std::lock_guard<std::mutex> lk(g_mu);
-    AuxStream* a = pair_stream(S, s0, s1);
-    if (!a || a->busy) return;
-    aux_ = a;
+    if (shared) aux_ = pair_stream(S, s0, s1);
+    if (!aux_ || aux_->busy) aux_ = S->own.get();
+    if (!aux_) return;
     aux_->busy = true;
+    st_ = aux_->st;
   }
   ~AuxLoan() {
     std::lock_guard<std::mutex> lk(g_mu);
-    aux_->busy = false;
+    if (aux_) aux_->busy = false;
   }
   AuxLoan(const AuxLoan&) = delete;
   AuxLoan& operator=(const AuxLoan&) = delete;
-  hipStream_t stream() const { return aux_->st; }
+  hipStream_t stream() const { return st_; }
 
  private:
-  AuxStream* aux_;
+  AuxStream* aux_ = nullptr;
+  hipStream_t st_;
 };
 
 char* block_input(merak_stage* S, int l) {
@@ -742,9 +750,9 @@ int merak_stage_create(const merak_stage_config* cfg, void* workspace, size_t wo
   S->timed_class = MERAK_KC_NONE;
   S->t_count = 0;
   S->t_overflow = false;
+  S->given = nullptr;
   hipError_t e = hipGetDevice(&S->dev);
   if (e == hipSuccess) e = make_aux(S->dev, &S->own);
-  if (e == hipSuccess) e = make_aux(S->dev, &S->spare);
   hipEvent_t* evs[] = {&S->ev_fork, &S->ev_s1, &S->ev_j0, &S->ev_j1, &S->ev_aux, &S->ev_dw[0], &S->ev_dw[1]};
   int made = 0;
   for (hipEvent_t* ev : evs) {

@@ -130,28 +130,22 @@ std::vector<hipStream_t> aux_streams(std::vector<Pair> callers) {
   return v;
 }
 
-// Handles on one pair share a stream; under capture each uses one that no other
-// call uses, before, during or after.
+// Handles on one pair share a stream, under graph capture too: every call on it is
+// then captured.  Calls on other streams use another meanwhile.
 void captured() {
   merak_stage_t h[3] = {create(0), create(1), create(2)};
   const Pair x = pair(), y = pair();
   aux_streams({});
-  for (merak_stage_t k : h) step(k, x);
+  for (merak_stage_t k : {h[0], h[1]}) step(k, x);
   const std::vector<hipStream_t> shared = aux_streams({x});
   EXPECT(shared.size() == 1);
   fake::run();
   fake::capture(x.s0, true);
-  std::vector<hipStream_t> own;
-  for (int i = 0; i < 2; ++i) {
-    step(h[i], x);
-    const std::vector<hipStream_t> a = aux_streams({x});
-    EXPECT(a.size() == 1 && a[0] != shared[0]);
-    for (hipStream_t o : own) EXPECT(a[0] != o);
-    own.push_back(a[0]);
-  }
-  step(h[2], y);  // eager, on other streams, meanwhile
+  for (merak_stage_t k : {h[0], h[1]}) step(k, x);
+  EXPECT(aux_streams({x}) == shared);
+  step(h[2], y);  // eager
   const std::vector<hipStream_t> other = aux_streams({y});
-  EXPECT(other.size() == 1 && other[0] != shared[0] && other[0] != own[0] && other[0] != own[1]);
+  EXPECT(other.size() == 1 && other != shared);
   fake::capture(x.s0, false);
   for (merak_stage_t k : h) step(k, x);
   EXPECT(aux_streams({x}) == shared);
@@ -187,13 +181,25 @@ void threads() {
   }
 }
 
-// A handle on more pairs than it keeps streams for, on the null stream, and on the
-// per-thread stream (never shared: its value names another stream in each thread).
+// Which stream a call takes: a handle alone takes its own from pair to pair; with
+// more pairs than handles the calls on the others run on the caller's streams; the
+// per-thread stream (whose value names another stream in each thread) is not shared.
 void many_pairs() {
-  merak_stage_t a = create(0), b = create(1);
+  merak_stage_t a = create(0);
   std::vector<Pair> ps;
   for (int i = 0; i < 12; ++i) ps.push_back(pair());
   ps.push_back({nullptr, nullptr});
+  aux_streams({});
+  step(a, ps[0]);
+  const std::vector<hipStream_t> own = aux_streams(ps);
+  EXPECT(own.size() == 1);
+  for (const Pair& p : ps) {
+    step(a, p);
+    EXPECT(aux_streams(ps) == own);
+    fake::run();
+    EXPECT(fake::idle(p.s0) && fake::idle(p.s1));
+  }
+  merak_stage_t b = create(1);
   for (int turn = 0; turn < 2; ++turn)
     for (const Pair& p : ps) {
       step(a, p);
@@ -201,16 +207,20 @@ void many_pairs() {
       fake::run();
       EXPECT(fake::idle(p.s0) && fake::idle(p.s1));
     }
-  EXPECT(fake::live_streams() <= 4);
+  EXPECT(fake::live_streams() == 2);
+  merak_stage_t c = create(2), d = create(3);
   const Pair per_thread{hipStreamPerThread, hipStreamPerThread};
   aux_streams({});
+  step(c, per_thread);
+  const std::vector<hipStream_t> sc = aux_streams({per_thread});
+  step(d, per_thread);
+  const std::vector<hipStream_t> sd = aux_streams({per_thread});
+  EXPECT(sc.size() == 1 && sd.size() == 1 && sc[0] != sd[0]);
   step(a, per_thread);
-  const std::vector<hipStream_t> sa = aux_streams({per_thread});
-  step(b, per_thread);
-  const std::vector<hipStream_t> sb = aux_streams({per_thread});
-  EXPECT(sa.size() == 1 && sb.size() == 1 && sa[0] != sb[0]);
+  EXPECT(aux_streams({per_thread}).empty());
   fake::run();
-  for (merak_stage_t h : {a, b}) EXPECT(merak_stage_destroy(h) == MERAK_OK);
+  EXPECT(fake::idle(hipStreamPerThread));
+  for (merak_stage_t h : {a, b, c, d}) EXPECT(merak_stage_destroy(h) == MERAK_OK);
 }
 
 // A creation that fails part-way leaves nothing behind.
@@ -218,12 +228,10 @@ void failed_create() {
   const merak_stage_config c = config();
   size_t ws = 0, rc = 0;
   EXPECT(merak_stage_workspace_bytes(&c, &ws, &rc) == MERAK_OK);
-  for (int n = 0; n < 2; ++n) {
-    fake::fail_stream_create_after(n);
-    merak_stage_t h = nullptr;
-    EXPECT(merak_stage_create(&c, dev(100), ws, dev(101), rc, &h) == MERAK_ERR_HIP && h == nullptr);
-    EXPECT(fake::live_streams() == 0 && fake::live_events() == 0);
-  }
+  fake::fail_stream_create_after(0);
+  merak_stage_t h = nullptr;
+  EXPECT(merak_stage_create(&c, dev(100), ws, dev(101), rc, &h) == MERAK_ERR_HIP && h == nullptr);
+  EXPECT(fake::live_streams() == 0 && fake::live_events() == 0);
   fake::fail_stream_create_after(-1);
 }
 

@@ -282,11 +282,12 @@ def test_backward_calls_of_several_handles(pairs):
 
 # The first run of the next two tests, with an earlier form of the stream
 # sharing, ended in a segmentation fault of the host process; which of the two
-# it was, and why, has not been shown.  That form is gone: under capture and on
-# pairs of streams of its own a handle's calls use a stream that no other call
-# uses.  The library's host code on both paths runs in test_host_streams.py,
-# against a stand-in for the HIP runtime, without a finding of the address and
-# thread sanitizers; the HIP runtime's part is not covered.
+# it was, and why, has not been shown.  That form is gone: a stream of the library
+# serves one pair of caller streams, so that calls on other pairs, from other host
+# threads or outside the capture, do not use it.  The library's host code on both
+# paths runs in test_host_streams.py, against a stand-in for the HIP runtime, without
+# a finding of the address and thread sanitizers; the HIP runtime's part is not
+# covered.
 _UNSHOWN = "ended the process with a segmentation fault in its first run; the cause has not been shown"
 
 
